@@ -34,12 +34,22 @@
 // column, the largest logit and its lowest vocabulary index; the same merges
 // carry it (the variant without it is the plain kernel).
 //
+// Slices.  Token tiles in whole groups of 16 take 16 vocabulary slices: one
+// group is one workgroup on each of the 256 compute units.  The r < 16 tiles
+// left over (all of them, for a call of up to 3840 tokens) would leave most of
+// the chip idle at 16 slices (one tile: 16 workgroups), so their vocabulary is
+// cut into as many slices as give up to 256 workgroups (plan_slices).  ms per
+// call on MI355X at V 128256, d 4096, 16 slices and this: 61 tokens 2.19 and
+// 0.24, 719 tokens 2.25 and 0.57, 2048 tokens 2.29 and 1.43, 5000 tokens 5.4
+// and 3.5, 9000 tokens 8.4 and 6.4.
+//
 // XCDs.  Workgroup ids are remapped so the 32 workgroups resident on one XCD
 // (ids are dealt round-robin over the 8 XCDs) cover 4 vocabulary slices x 8
 // token tiles, and one dispatch wave of 256 covers 16 x 16: concurrent
 // workgroups stream the same W and X tiles through that XCD's L2.  An XCD
 // takes the slices g, g+4, g+8, g+12, so the slices that hold one tile more
 // than the others are spread over the XCDs.
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -52,7 +62,9 @@ namespace detail {
 constexpr int kBV = 256;       // vocabulary rows per tile
 constexpr int kBT = 256;       // tokens per tile
 constexpr int kWaves = 4;      // waves per workgroup, one per SIMD
-constexpr int kMaxVsplit = 16;
+constexpr int kMaxVsplit = 16;  // vocabulary slices of a whole group of token tiles
+constexpr int kGroupTiles = 16; // token tiles of a group: kGroupTiles * kMaxVsplit workgroups are one per CU
+constexpr int kTailWgs = 256;   // workgroups the token tiles past the last whole group are split into
 constexpr int kNB = 8;         // 16-row blocks per wave, both operands (128 rows each)
 constexpr int kMfmaPerStep = kNB * kNB;
 
@@ -97,6 +109,58 @@ __device__ __forceinline__ void arg_merge(float& av, int& ai, float bv, int bi) 
   ai = take ? bi : ai;
 }
 
+// How one call's token tiles are cut into workgroups.  The first main_tiles tiles (whole groups of
+// kGroupTiles) take kMaxVsplit vocabulary slices each, the rest tail_slices; the partial states are
+// [kMaxVsplit, main tokens] followed by [tail_slices, tail tokens].
+struct SlicePlan {
+  int main_tiles;
+  int tail_slices;
+  int tail_cols;  // token tiles of one slice that run next to each other on one XCD (0: plain order)
+};
+
+// Partial states per array that a call's workspace holds: kMaxVsplit per token and, while the
+// no-allocation entry point's fixed scratch has room for it, what kTailWgs workgroups of one token
+// tile each write.  Grows with n_tok, so a workspace sized for more tokens serves fewer.
+constexpr int64_t kTailMaxTok = 384 * kBT;
+inline size_t partial_capacity(int64_t n_tok, int n_vt) {
+  if (n_vt <= kMaxVsplit) return size_t(n_vt) * size_t(n_tok);
+  const size_t plain = size_t(kMaxVsplit) * size_t(n_tok);
+  const size_t capped = size_t(kMaxVsplit) * size_t(n_tok < kTailMaxTok ? n_tok : kTailMaxTok);
+  const size_t split = capped + size_t(kTailWgs) * kBT;
+  return plain > split ? plain : split;
+}
+
+// Slices of the n_tt token tiles.  With r tiles left over, tail_slices x r stays within kTailWgs
+// (one workgroup per CU), and among slice counts with the same largest number of vocabulary tiles
+// per workgroup the smallest is taken.  Vocabularies of up to kMaxVsplit tiles take one slice per
+// tile, and calls whose tail states would not fit the workspace kMaxVsplit.
+inline SlicePlan plan_slices(int64_t n_tok, int n_vt) {
+  const int n_tt = int((n_tok + kBT - 1) / kBT);
+  SlicePlan p;
+  p.main_tiles = n_vt >= kMaxVsplit ? n_tt / kGroupTiles * kGroupTiles : 0;
+  p.tail_slices = n_vt < kMaxVsplit ? n_vt : kMaxVsplit;
+  p.tail_cols = 0;
+  const int r = n_tt - p.main_tiles;
+  if (r > 0 && n_vt > kMaxVsplit) {
+    const int most = kTailWgs / r < n_vt ? kTailWgs / r : n_vt;
+    const int per_wg = (n_vt + most - 1) / most;
+    const int slices = (n_vt + per_wg - 1) / per_wg;
+    const int64_t main_tok = int64_t(p.main_tiles) * kBT;
+    if (slices > kMaxVsplit &&
+        size_t(kMaxVsplit) * main_tok + size_t(slices) * (n_tok - main_tok) <= partial_capacity(n_tok, n_vt)) {
+      p.tail_slices = slices;
+      p.tail_cols = r <= 8 ? r : (r + 1) / 2;  // one or two groups of up to 8 tiles
+    }
+  }
+  return p;
+}
+
+// Workgroups of the bf16 kernel's grid.
+inline size_t plan_workgroups(const SlicePlan& p, int64_t n_tok) {
+  const size_t r = size_t((n_tok + kBT - 1) / kBT) - size_t(p.main_tiles), n_wg = r * size_t(p.tail_slices);
+  return size_t(p.main_tiles) * kMaxVsplit + (p.tail_cols == 0 ? n_wg : (n_wg + 7) / 8 * 8);
+}
+
 // A stage is BK deep (kSub k steps).  Ring of P part slots: part 2s + 0 / 2s + 1
 // (W / X of stage s) lives in slot (2s + o) % P.  Within a stage the wave runs
 // kSub k steps, each reading the next step's fragments while its MFMAs run.
@@ -107,7 +171,7 @@ __device__ __forceinline__ void arg_merge(float& av, int& ai, float bv, int bi) 
 // (P - 2) / 2 stages of loads are in flight while a stage is consumed.
 template <int P, int BK, bool kArg>
 __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
-    const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int n_tok, int d, int V, int n_vsplit,
+    const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int n_tok, int d, int V, SlicePlan pl,
     int n_vt, int n_tt, float* __restrict__ part_m, float* __restrict__ part_s, float* __restrict__ part_t,
     float* __restrict__ part_zmax, int* __restrict__ part_arg) {
   using G = Geom<BK>;
@@ -126,25 +190,54 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
   const int wt = wave >> 1;  // which 128-token half of the token tile
 
   // ---- workgroup -> (vocabulary slice, token tile)
-  int vs, tt;
+  int vs, tt, n_vsplit;
+  size_t part_off;   // this workgroup's row of the partial states, less its first token
   {
     const int bid = blockIdx.x;
     constexpr int R = 32;  // workgroups resident on one XCD
-    // whole dispatch waves of 16 token tiles x 16 slices take the XCD-aware order; the
-    // token tiles past the last whole group of 16 (ragged batches) follow in plain order
-    const int n_full = n_vsplit == 16 ? (n_tt / (R / 2)) * (R / 2) * 16 : 0;
-    if (bid < n_full) {
+    const int n_main = pl.main_tiles * kMaxVsplit;
+    if (bid < n_main) {
+      // whole dispatch waves of 16 token tiles x 16 slices
       const int xcd = bid & 7, j = bid >> 3;
       const int wave_idx = j / R, jj = j % R;
+      n_vsplit = kMaxVsplit;
       vs = (jj & 3) * 4 + (xcd & 3);
       tt = wave_idx * (R / 2) + (xcd >> 2) * (R / 4) + (jj >> 2);
+      part_off = size_t(vs) * min(n_tok, pl.main_tiles * kBT);
     } else {
-      const int r = bid - n_full;
-      vs = r % n_vsplit;
-      tt = n_full / n_vsplit + r / n_vsplit;
+      // the tiles past them
+      int r = bid - n_main, in_tail;
+      n_vsplit = pl.tail_slices;
+      if (pl.tail_cols == 0) {  // plain order, slice fastest
+        vs = r % n_vsplit;
+        in_tail = r / n_vsplit;
+      } else {
+        // an eighth of the workgroups to each XCD (n_main is a multiple of 8), in an order that
+        // puts the tail_cols token tiles of one slice next to each other: they stream the same
+        // rows of W through one L2.  The second group of columns holds what is left of the tiles.
+        const int n_wg = (n_tt - pl.main_tiles) * n_vsplit, per_xcd = (n_wg + 7) / 8;
+        r = (r & 7) * per_xcd + (r >> 3);
+        if (r >= n_wg) return;  // the grid is rounded up
+        const int n_first = pl.tail_cols * n_vsplit;
+        const bool second = r >= n_first;
+        const int cols = second ? n_tt - pl.main_tiles - pl.tail_cols : pl.tail_cols;
+        if (second) r -= n_first;
+        vs = r / cols;
+        in_tail = (second ? pl.tail_cols : 0) + r % cols;
+      }
+      tt = pl.main_tiles + in_tail;
+      const int first = pl.main_tiles * kBT;
+      part_off = size_t(kMaxVsplit) * first + size_t(vs) * (n_tok - first) - first;
     }
   }
   const int nk = d / BK;
+  // Depth stage this workgroup starts every tile at (it wraps around).  A lone token tile streams
+  // W once, from HBM, with every workgroup on rows of its own: all at the same depth, their
+  // addresses differ by multiples of the row stride only and crowd on part of the memory channels
+  // (d 4096, V 128256, 256 tokens on MI355X: 320 us, with staggered starts 250).  With more tiles
+  // the workgroups of a slice share W, and those on one XCD the stages of X, through L2: staggered
+  // starts lose that (1024 tokens: 768 and 828 us), so they all start at 0.
+  const int ks0 = pl.main_tiles == 0 && pl.tail_cols == 1 ? (vs * 5) % nk : 0;
   const int n_my_tiles = (n_vt - vs + n_vsplit - 1) / n_vsplit;
   const size_t row_stride = size_t(d) * 2;  // bytes per row of W and X
 
@@ -169,7 +262,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
   // resource (no memory access, zeros into the slot being freed, never read),
   // so every barrier issues exactly 2 L transfers per wave and the waits below
   // are the same on every stage; the loop body stays one basic block.
-  int pf_tile = 0, pf_ks = 0, pf_slot = 0, pf_op = 0;
+  int pf_tile = 0, pf_ks = ks0, pf_slot = 0, pf_op = 0;
   int pf_vt = vs;                                                                  // vocabulary tile of the prefetch
   const char* pf_w = reinterpret_cast<const char*>(W) + size_t(vs) * tile_bytes;  // its rows of W
   const size_t w_step = size_t(n_vsplit) * tile_bytes;
@@ -191,9 +284,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
       p.rsrc = make_rsrc(pf_w, rows * uint32_t(row_stride));
     } else {
       p.rsrc = live ? rx : r_none;
-      const bool wrap = pf_ks + 1 == nk;
-      pf_ks = wrap ? 0 : pf_ks + 1;
-      if (wrap) {
+      pf_ks = pf_ks + 1 == nk ? 0 : pf_ks + 1;
+      if (pf_ks == ks0) {
         ++pf_tile;
         pf_vt += n_vsplit;
         pf_w += w_step;
@@ -495,7 +587,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
       Ent2 r = ent2_merge(st[j], Ent2{p[0], p[1], p[2]});
       const int tok = tt * kBT + tl;
       if (tok < n_tok) {
-        const size_t o = size_t(vs) * n_tok + tok;
+        const size_t o = part_off + tok;
         part_m[o] = r.m;
         part_s[o] = r.s;
         part_t[o] = r.t;
@@ -512,7 +604,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
         float zb = zmax[c];
         int ib = zarg[c];
         arg_merge(zb, ib, p[3], __float_as_int(p[4]));
-        const size_t o = size_t(vs) * n_tok + tok;
+        const size_t o = part_off + tok;
         part_zmax[o] = zb;
         part_arg[o] = ib;
       }
@@ -520,33 +612,67 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
   }
 }
 
-// Merge the n_vsplit partial states of each token and write H in nats:
-// H = ln2 * (log2 s - t / s).  With `arg` non-null, also the vocabulary index
-// of the largest logit over the slices (lowest index among equal maxima).
+// Merge the partial states of each token and write H in nats: H = ln2 * (log2 s - t / s).  With
+// `arg` non-null, also the vocabulary index of the largest logit over the slices (lowest index
+// among equal maxima).  The tokens are first .. first + n, their states [n_slices, n].  kLanes
+// threads share a token: thread group q merges slices q, q + kLanes, ... in order, then the groups
+// merge in order (within a wave by lane exchange, then the four waves through LDS).  One thread per
+// token for 16 slices; 16 where a small call has up to 256 (61 and 719 tokens, 251 and 84 slices, on
+// MI355X: 21 us with one thread per token, 5.6 with 16).
+template <int kLanes>
 __global__ __launch_bounds__(256) void entropy_merge_kernel(const float* __restrict__ part_m,
                                                             const float* __restrict__ part_s,
                                                             const float* __restrict__ part_t,
                                                             const float* __restrict__ part_zmax,
-                                                            const int* __restrict__ part_arg, int n_tok,
-                                                            int n_vsplit, float* __restrict__ H,
+                                                            const int* __restrict__ part_arg, int first, int n,
+                                                            int n_slices, float* __restrict__ H,
                                                             int32_t* __restrict__ arg) {
-  const int tok = blockIdx.x * 256 + threadIdx.x;
-  if (tok >= n_tok) return;
-  Ent2 a{part_m[tok], part_s[tok], part_t[tok]};
-  for (int v = 1; v < n_vsplit; ++v) {
-    const size_t o = size_t(v) * n_tok + tok;
-    a = ent2_merge(a, Ent2{part_m[o], part_s[o], part_t[o]});
-  }
-  H[tok] = kLn2 * (fast_log2(a.s) - a.t / a.s);
-  if (arg) {
-    float zb = part_zmax[tok];
-    int ib = part_arg[tok];
-    for (int v = 1; v < n_vsplit; ++v) {
-      const size_t o = size_t(v) * n_tok + tok;
-      arg_merge(zb, ib, part_zmax[o], part_arg[o]);
+  static_assert(kLanes == 1 || kLanes == 16, "four groups per wave or none");
+  constexpr int kToks = 256 / kLanes;
+  const int t = threadIdx.x % kToks, q = threadIdx.x / kToks;
+  const int tok = blockIdx.x * kToks + t;
+  Ent2 a{-INFINITY, 0.f, 0.f};
+  float zb = -INFINITY;
+  int ib = INT32_MAX;
+  if (tok < n) {
+    if (q < n_slices) a = Ent2{part_m[size_t(q) * n + tok], part_s[size_t(q) * n + tok], part_t[size_t(q) * n + tok]};
+#pragma unroll 4
+    for (int v = q + kLanes; v < n_slices; v += kLanes) {
+      const size_t o = size_t(v) * n + tok;
+      a = ent2_merge(a, Ent2{part_m[o], part_s[o], part_t[o]});
     }
-    arg[tok] = ib;
+    if (arg)
+      for (int v = q; v < n_slices; v += kLanes) {
+        const size_t o = size_t(v) * n + tok;
+        arg_merge(zb, ib, part_zmax[o], part_arg[o]);
+      }
   }
+  if (kLanes > 1) {
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {
+      a = ent2_merge(a, Ent2{__shfl_xor(a.m, o, 64), __shfl_xor(a.s, o, 64), __shfl_xor(a.t, o, 64)});
+      arg_merge(zb, ib, __shfl_xor(zb, o, 64), __shfl_xor(ib, o, 64));
+    }
+    __shared__ float sh[5][4][kToks];
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) < kToks) {
+      sh[0][wave][t] = a.m;
+      sh[1][wave][t] = a.s;
+      sh[2][wave][t] = a.t;
+      sh[3][wave][t] = zb;
+      sh[4][wave][t] = __int_as_float(ib);
+    }
+    __syncthreads();
+    if (threadIdx.x >= kToks) return;
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {
+      a = ent2_merge(a, Ent2{sh[0][w][t], sh[1][w][t], sh[2][w][t]});
+      arg_merge(zb, ib, sh[3][w][t], __float_as_int(sh[4][w][t]));
+    }
+  }
+  if (tok >= n) return;
+  H[first + tok] = kLn2 * (fast_log2(a.s) - a.t / a.s);
+  if (arg) arg[first + tok] = ib;
 }
 
 int choose_vsplit(int n_vt) { return n_vt < kMaxVsplit ? n_vt : kMaxVsplit; }
@@ -564,7 +690,7 @@ extern "C" size_t estp_token_entropy_workspace_size(int64_t n_tok, int32_t d, in
   const int n_vt = (V + kBV - 1) / kBV;
   Carver c(nullptr);
   // per-slice (m, s, t) states, then the per-slice largest logit and its index
-  for (int i = 0; i < 5; ++i) c.take<float>(size_t(choose_vsplit(n_vt)) * n_tok);
+  for (int i = 0; i < 5; ++i) c.take<float>(partial_capacity(n_tok, n_vt));
   return c.bytes();
 }
 
@@ -586,9 +712,9 @@ int check_entropy_args(const char* fn, const void* X, const void* W, int64_t n_t
   ESTP_REQUIRE(aligned(H, 4) && aligned(vocab_argmax, 4), ESTP_ERR_INVALID_ARG,
                "%s: H and vocab_argmax must be 4-byte aligned", fn);
   const int n = int(n_tok);
-  const int n_vsplit = choose_vsplit((V + kBV - 1) / kBV);
-  const size_t n_wg =
-      dtype == ESTP_F32 ? entropy_f32_workgroups(n, n_vsplit) : size_t(n_vsplit) * size_t((n + kBT - 1) / kBT);
+  const int n_vt = (V + kBV - 1) / kBV;
+  const size_t n_wg = dtype == ESTP_F32 ? entropy_f32_workgroups(n, choose_vsplit(n_vt))
+                                        : plan_workgroups(plan_slices(n, n_vt), n);
   ESTP_REQUIRE(fits_launch(n_wg, kWaves * 64), ESTP_ERR_UNSUPPORTED,
                "%s: n_tok = %d needs %zu workgroups, more than one launch holds", fn, n, n_wg);
   return ESTP_OK;
@@ -600,42 +726,56 @@ int launch_token_entropy(const void* X, const void* W, int n, int d, int V, int 
                          int32_t* vocab_argmax, void* workspace, hipStream_t s) {
   const int n_vt = (V + kBV - 1) / kBV;
   const int n_tt = (n + kBT - 1) / kBT;
-  const int n_vsplit = choose_vsplit(n_vt);
+  const size_t cap = partial_capacity(n, n_vt);
   Carver c(workspace);
-  float* pm = c.take<float>(size_t(n_vsplit) * n);
-  float* ps = c.take<float>(size_t(n_vsplit) * n);
-  float* pt = c.take<float>(size_t(n_vsplit) * n);
-  float* pz = c.take<float>(size_t(n_vsplit) * n);
-  int* pa = c.take<int>(size_t(n_vsplit) * n);
+  float* pm = c.take<float>(cap);
+  float* ps = c.take<float>(cap);
+  float* pt = c.take<float>(cap);
+  float* pz = c.take<float>(cap);
+  int* pa = c.take<int>(cap);
   const bool want_arg = vocab_argmax != nullptr;
 
+  // one merge per token range with the same number of slices
+  auto merge = [&](int first, int count, int n_slices, size_t off) {
+    if (count <= 0) return;
+    const int* pa_m = want_arg ? pa + off : nullptr;
+    if (n_slices <= kMaxVsplit)
+      entropy_merge_kernel<1><<<dim3((count + 255) / 256), dim3(256), 0, s>>>(
+          pm + off, ps + off, pt + off, pz + off, pa_m, first, count, n_slices, H, vocab_argmax);
+    else
+      entropy_merge_kernel<16><<<dim3((count + 15) / 16), dim3(256), 0, s>>>(
+          pm + off, ps + off, pt + off, pz + off, pa_m, first, count, n_slices, H, vocab_argmax);
+  };
+
   if (dtype == ESTP_F32) {
+    const int n_vsplit = choose_vsplit(n_vt);
     launch_entropy_f32(static_cast<const float*>(X), static_cast<const float*>(W), n, d, V, n_vsplit, pm, ps, pt, pz,
                        want_arg ? pa : nullptr, s);
     ESTP_CHECK_LAUNCH("entropy_f32_kernel");
+    merge(0, n, n_vsplit, 0);
   } else {
-    const dim3 grid(n_vsplit * n_tt), block(kWaves * 64);
+    const SlicePlan pl = plan_slices(n, n_vt);
+    const dim3 grid(unsigned(plan_workgroups(pl, n))), block(kWaves * 64);
     const uint16_t* Xh = static_cast<const uint16_t*>(X);
     const uint16_t* Wh = static_cast<const uint16_t*>(W);
     if (d % 64 == 0) {
       if (want_arg)
-        entropy_gemm_kernel<5, 64, true><<<grid, block, 0, s>>>(Xh, Wh, n, d, V, n_vsplit, n_vt, n_tt, pm, ps, pt, pz,
-                                                                pa);
+        entropy_gemm_kernel<5, 64, true><<<grid, block, 0, s>>>(Xh, Wh, n, d, V, pl, n_vt, n_tt, pm, ps, pt, pz, pa);
       else
-        entropy_gemm_kernel<5, 64, false><<<grid, block, 0, s>>>(Xh, Wh, n, d, V, n_vsplit, n_vt, n_tt, pm, ps, pt,
-                                                                 nullptr, nullptr);
+        entropy_gemm_kernel<5, 64, false><<<grid, block, 0, s>>>(Xh, Wh, n, d, V, pl, n_vt, n_tt, pm, ps, pt, nullptr,
+                                                                 nullptr);
     } else {
       if (want_arg)
-        entropy_gemm_kernel<9, 32, true><<<grid, block, 0, s>>>(Xh, Wh, n, d, V, n_vsplit, n_vt, n_tt, pm, ps, pt, pz,
-                                                                pa);
+        entropy_gemm_kernel<9, 32, true><<<grid, block, 0, s>>>(Xh, Wh, n, d, V, pl, n_vt, n_tt, pm, ps, pt, pz, pa);
       else
-        entropy_gemm_kernel<9, 32, false><<<grid, block, 0, s>>>(Xh, Wh, n, d, V, n_vsplit, n_vt, n_tt, pm, ps, pt,
-                                                                 nullptr, nullptr);
+        entropy_gemm_kernel<9, 32, false><<<grid, block, 0, s>>>(Xh, Wh, n, d, V, pl, n_vt, n_tt, pm, ps, pt, nullptr,
+                                                                 nullptr);
     }
     ESTP_CHECK_LAUNCH("entropy_gemm_kernel");
+    const int n_main = std::min(n, pl.main_tiles * kBT);
+    merge(0, n_main, kMaxVsplit, 0);
+    merge(n_main, n - n_main, pl.tail_slices, size_t(kMaxVsplit) * n_main);
   }
-  entropy_merge_kernel<<<dim3((n + 255) / 256), dim3(256), 0, s>>>(pm, ps, pt, pz, want_arg ? pa : nullptr, n,
-                                                                   n_vsplit, H, vocab_argmax);
   ESTP_CHECK_LAUNCH("entropy_merge_kernel");
   return ESTP_OK;
 }
