@@ -122,12 +122,27 @@ struct SlicePlan {
 // no-allocation entry point's fixed scratch has room for it, what kTailWgs workgroups of one token
 // tile each write.  Grows with n_tok, so a workspace sized for more tokens serves fewer.
 constexpr int64_t kTailMaxTok = 384 * kBT;
+constexpr int64_t kFineMaxTok = 4096;
 inline size_t partial_capacity(int64_t n_tok, int n_vt) {
-  if (n_vt <= kMaxVsplit) return size_t(n_vt) * size_t(n_tok);
+  if (n_vt <= kMaxVsplit) {
+    // fp32 calls of a few tokens over a small vocabulary cut it finer than 256 rows (f32_max_slices)
+    const size_t fine = size_t(n_tok < kFineMaxTok ? n_tok : kFineMaxTok) * kMaxVsplit;
+    const size_t plain = size_t(n_vt) * size_t(n_tok);
+    return plain > fine ? plain : fine;
+  }
   const size_t plain = size_t(kMaxVsplit) * size_t(n_tok);
   const size_t capped = size_t(kMaxVsplit) * size_t(n_tok < kTailMaxTok ? n_tok : kTailMaxTok);
   const size_t split = capped + size_t(kTailWgs) * kBT;
   return plain > split ? plain : split;
+}
+
+// Most vocabulary slices of an fp32 call: as many as give its (64-token) tiles two workgroups per CU,
+// at least kMaxVsplit, and no more states than the workspace holds.
+inline int f32_max_slices(int64_t n_tok, int n_vt) {
+  if (n_vt < kMaxVsplit) return n_tok > kFineMaxTok ? n_vt : kMaxVsplit;
+  const int64_t want = 2 * kTailWgs / ((n_tok + 63) / 64), room = int64_t(partial_capacity(n_tok, n_vt)) / n_tok;
+  const int64_t most = want < room ? want : room;
+  return int(most > kMaxVsplit ? most : kMaxVsplit);
 }
 
 // Slices of the n_tt token tiles.  With r tiles left over, tail_slices x r stays within kTailWgs
@@ -675,8 +690,6 @@ __global__ __launch_bounds__(256) void entropy_merge_kernel(const float* __restr
   if (arg) arg[first + tok] = ib;
 }
 
-int choose_vsplit(int n_vt) { return n_vt < kMaxVsplit ? n_vt : kMaxVsplit; }
-
 }  // namespace detail
 }  // namespace estp
 
@@ -713,7 +726,7 @@ int check_entropy_args(const char* fn, const void* X, const void* W, int64_t n_t
                "%s: H and vocab_argmax must be 4-byte aligned", fn);
   const int n = int(n_tok);
   const int n_vt = (V + kBV - 1) / kBV;
-  const size_t n_wg = dtype == ESTP_F32 ? entropy_f32_workgroups(n, choose_vsplit(n_vt))
+  const size_t n_wg = dtype == ESTP_F32 ? entropy_f32_workgroups(n, V, f32_max_slices(n, n_vt))
                                         : plan_workgroups(plan_slices(n, n_vt), n);
   ESTP_REQUIRE(fits_launch(n_wg, kWaves * 64), ESTP_ERR_UNSUPPORTED,
                "%s: n_tok = %d needs %zu workgroups, more than one launch holds", fn, n, n_wg);
@@ -748,11 +761,11 @@ int launch_token_entropy(const void* X, const void* W, int n, int d, int V, int 
   };
 
   if (dtype == ESTP_F32) {
-    const int n_vsplit = choose_vsplit(n_vt);
-    launch_entropy_f32(static_cast<const float*>(X), static_cast<const float*>(W), n, d, V, n_vsplit, pm, ps, pt, pz,
+    const int most = f32_max_slices(n, n_vt);
+    launch_entropy_f32(static_cast<const float*>(X), static_cast<const float*>(W), n, d, V, most, pm, ps, pt, pz,
                        want_arg ? pa : nullptr, s);
     ESTP_CHECK_LAUNCH("entropy_f32_kernel");
-    merge(0, n, n_vsplit, 0);
+    merge(0, n, entropy_f32_slices(n, V, most), 0);
   } else {
     const SlicePlan pl = plan_slices(n, n_vt);
     const dim3 grid(unsigned(plan_workgroups(pl, n))), block(kWaves * 64);

@@ -22,43 +22,6 @@ namespace detail {
 
 constexpr int kKChunk = 256;  // the depth of the first layer is never split finer over workgroups than this
 
-// v_mfma_f32_32x32x2_f32: c[m][n] += sum over 2 k of a[m][k] b[k][n], all fp32.  Lane l gives a row
-// m (b: column n) l % 32 at k = l / 32, and holds rows 8 (r / 4) + 4 (l / 32) + r % 4 of column l % 32.
-__device__ __forceinline__ f32x16_t mfma32_f32(float a, float b, const f32x16_t& c) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-#else
-  return c;
-#endif
-}
-// v_mfma_f32_16x16x4_f32: the same over 4 k.  Lane l gives row (column) l % 16 at k = l / 16 and holds rows
-// 4 (l / 16) + r of column l % 16.
-__device__ __forceinline__ f32x4_t mfma16_f32(float a, float b, const f32x4_t& c) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-#else
-  return c;
-#endif
-}
-__device__ __forceinline__ int mfma_row(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
-
-// 16- and 4-byte loads at a byte offset of a buffer resource; kPastEnd is past the end of any resource here.
-constexpr uint32_t kPastEnd = 0xfffffff0u;
-__device__ __forceinline__ f32x4_t buf_load4(buf_rsrc_t r, uint32_t off) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
-#else
-  return f32x4_t{};
-#endif
-}
-__device__ __forceinline__ float buf_load1(buf_rsrc_t r, uint32_t off) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
-#else
-  return 0.f;
-#endif
-}
-
 __device__ __forceinline__ float act_fn(float x, int act) {
   if (act == ESTP_ACT_RELU) return fmaxf(x, 0.f);
   // tanh-form GELU: 0.5 x (1 + tanh(sqrt(2/pi) (x + 0.044715 x^3)))

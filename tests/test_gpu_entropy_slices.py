@@ -1,5 +1,5 @@
-"""Vocabulary slices of the bf16 entropy call against the fp64 oracle, where the split changes:
-the token tiles past the last whole group of 16 take as many slices as give up to 256 workgroups."""
+"""Vocabulary slices of the entropy call against the fp64 oracle, where the split changes: bf16, the token
+tiles past the last whole group of 16 take as many slices as give up to 256 workgroups."""
 import numpy as np
 import pytest
 import torch
@@ -23,22 +23,29 @@ CASES = [
 ]
 
 
-@pytest.mark.gpu
-@pytest.mark.parametrize("n,d,V", CASES, ids=["x".join(map(str, c)) for c in CASES])
-def test_entropy_slices(n, d, V):
-    g = np.random.default_rng(n + V)
-    X = g.standard_normal((n, d)).astype(np.float32)
-    X = I.f32_to_bf16_bits(X / np.sqrt((X * X).mean(axis=1, keepdims=True)))
-    W = I.f32_to_bf16_bits(g.standard_normal((V, d)).astype(np.float32) * 0.3)
+# fp32: tiles of 64 x 64 (calls that 128 x 128 tiles would not spread over the chip) and of 128 x 128
+CASES_F32 = [
+    (1, 8, 1),
+    (63, 40, 65),        # depth ends inside a step
+    (65, 72, 129),       # one token and one word past a tile
+    (129, 64, 16500),    # 170 slices
+    (4097, 32, 300),     # few vocabulary tiles: no more slices than 256-row tiles
+    (2100, 32, 33000),   # 128 x 128 tiles, ragged both ways
+]
+
+
+def _check(X, W, n, V):
     am = torch.full((n,), -7, dtype=torch.int32, device="cuda")
     Xd, Wd = dev(X), dev(W)
     H = estp.token_entropy(Xd, Wd, vocab_argmax=am)
     rows = np.unique(np.concatenate([np.arange(min(n, 40)), np.arange(max(0, n - 300), n), np.arange(0, n, 61)]))
     ref = oracle.token_entropy(X[rows], W)
     # H moves by at most sum_v p_v |z_v - E z| |dz| <= (ln V + max z - min z) max|dz| with logit errors
-    # below half logit_error_bound; the exp2, log2 and sums of positive terms add a few hundred ulp of H
+    # below half logit_error_bound; the exp2, log2 and sums of positive terms add a few hundred ulp of H,
+    # and of 1 where H itself is small
     z = oracle.widen(X[rows]) @ oracle.widen(W).T
-    bound = (np.log(V) + z.max(axis=1) - z.min(axis=1)) * logit_error_bound(X, W, rows) / 2 + 300 * 2.0 ** -24 * ref
+    bound = ((np.log(V) + z.max(axis=1) - z.min(axis=1)) * logit_error_bound(X, W, rows) / 2
+             + 300 * 2.0 ** -24 * np.maximum(ref, 1.0))
     err = np.abs(host(H)[rows] - ref)
     print(f"max |dH| / bound = {(err / bound).max():.3g}")
     assert np.all(err <= bound)
@@ -46,6 +53,26 @@ def test_entropy_slices(n, d, V):
     # without the mode, and on the library's own scratch: the same bits
     assert torch.equal(estp.token_entropy(Xd, Wd), H)
     assert torch.equal(estp.token_entropy_noalloc(Xd, Wd, torch.empty_like(H)), H)
+
+
+def _inputs(n, d, V):
+    g = np.random.default_rng(n + V)
+    X = g.standard_normal((n, d)).astype(np.float32)
+    return X / np.sqrt((X * X).mean(axis=1, keepdims=True)), g.standard_normal((V, d)).astype(np.float32) * 0.3
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,d,V", CASES, ids=["x".join(map(str, c)) for c in CASES])
+def test_entropy_slices(n, d, V):
+    X, W = _inputs(n, d, V)
+    _check(I.f32_to_bf16_bits(X), I.f32_to_bf16_bits(W), n, V)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,d,V", CASES_F32, ids=["x".join(map(str, c)) for c in CASES_F32])
+def test_entropy_slices_f32(n, d, V):
+    X, W = _inputs(n, d, V)
+    _check(X, W, n, V)
 
 
 def test_entropy_workspace_grows_with_tokens():
