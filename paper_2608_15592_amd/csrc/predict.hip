@@ -33,12 +33,12 @@ __device__ __forceinline__ float act_fn(float x, int act) {
 // A workgroup forms a 16 NB x 16 NB (prompt x hidden) tile; its kDW waves take consecutive depth ranges of
 // kw and their tiles are added in wave order through LDS.  Both operands are contiguous along the depth, so
 // a lane loads 16 bytes of its row and the four floats feed four matrix-core steps (step i multiplies depths
-// k + i, k + 4 + i, k + 8 + i and k + 12 + i): no LDS staging and no transposition, and the next 32 depths
-// (one 128-byte line of each row) load while the current ones multiply.  The fp32 matrix cores have the
+// k + i, k + 4 + i, k + 8 + i and k + 12 + i): no LDS staging and no transposition, and the next 16 or 32
+// depths load while the current ones multiply.  The fp32 matrix cores have the
 // rate of the fp32 vector FMAs but read each operand once per 16 products; the vector form (32 x 32 tiles
 // through LDS, five 4-byte LDS reads per four FMAs) was bound by LDS: us per estp_predict call on MI355X,
-// 4096 -> 1024 -> 16, that form and this: one prompt 31 and 12, 64 prompts 46 and 19, 256 prompts 116 and 39,
-// 2048 prompts 695 and 222 (109 of it fp32 arithmetic at the peak rate).
+// 4096 -> 1024 -> 16, that form and this: one prompt 31 and 12, 64 prompts 46 and 19, 256 prompts 116 and 33,
+// 2048 prompts 695 and 173 (109 of it fp32 arithmetic at the peak rate).
 template <int NB, int kDW, bool kVec>
 __global__ __launch_bounds__(64 * kDW) void mlp_partial_kernel(const float* __restrict__ P,
                                                                const float* __restrict__ W1, int B, int d, int Hd,
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(64 * kDW) void mlp_partial_kernel(const float* __re
     for (int c = 0; c < 4; ++c) v[c] = buf_load1(r, k + c < k_hi ? off + 4 * c : kPastEnd);
     return v;
   };
-  constexpr int kHalves = 2;
+  constexpr int kHalves = NB == 4 ? 1 : 2;  // NB = 4: two whole-line steps would spill
   struct Step {
     f32x4_t a[kHalves][NB], b[kHalves][NB];
   };
@@ -155,7 +155,7 @@ int launch_mlp_tiles(const float* P, const float* W1, int B, int d, int Hd, floa
 }
 // Tiles of 64 x 64, which read half as much per product, where there are at least 64 of them; else of 32 x 32,
 // which spread over more CUs (us per estp_predict call on MI355X with 32 and with 64: 4096 -> 1024, 2048
-// prompts 281 and 222, 256 prompts 42 and 39, one prompt 12 and 16; 1536 -> 256, 256 prompts 17 and 20).
+// prompts 281 and 173, 256 prompts 42 and 33, one prompt 12 and 16; 1536 -> 256, 256 prompts 17 and 20).
 int launch_mlp_partial(const float* P, const float* W1, int B, int d, int Hd, float* part, hipStream_t s) {
   const bool wide = ((size_t(B) + 63) / 64) * ((size_t(Hd) + 63) / 64) >= 64;
   return wide ? launch_mlp_tiles<4, 8>(P, W1, B, d, Hd, part, s) : launch_mlp_tiles<2, 16>(P, W1, B, d, Hd, part, s);
