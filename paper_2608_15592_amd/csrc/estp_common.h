@@ -97,6 +97,13 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | 0x0F70);
 }
 
+// The same, and every LDS operation of this wave done (lgkmcnt 0).
+template <int N>
+__device__ __forceinline__ void wait_vm_lds() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | 0x0070);
+}
+
 // Workgroup barrier that leaves outstanding global loads in flight (unlike
 // __syncthreads, whose fence drains them): waits only for this wave's LDS
 // operations, then s_barrier.  The signal fences keep the compiler from moving
