@@ -1,7 +1,9 @@
 // Attention importance, Eq. 1 (Section 4.1):
 //   S_j = sum_l (1/N) sum_{i >= j} (1/Hq) sum_h A^{l,h}_{ij}
 // with A the causal softmax of scale * q_i . k_j inside each prompt, without
-// ever forming the N x N attention.
+// ever forming the N x N attention.  Most batches of bf16 prompts of up to 2048
+// tokens take one pass (importance_onepass.hip); this file holds the two passes
+// for the others and the entry points.
 //
 // Pass 1 (attn_lse_kernel): one workgroup per (layer, query head, prompt,
 // 256-query block); each of its 4 waves keeps 64 queries as matrix-core B
@@ -26,7 +28,7 @@
 // others' matrix-core work.
 #include <algorithm>
 
-#include "estp_common.h"
+#include "attn_tiles.h"
 #include "f32_paths.h"
 
 namespace estp {
@@ -67,6 +69,10 @@ inline size_t block_rows(int64_t n_tok, int32_t B, int32_t max_seqlen) {
   return use_block_list(n_tok, B, max_seqlen) ? block_bound(n_tok, B, max_seqlen) : size_t(B) * nqb;
 }
 
+// Column-mass rows of a call: one per (layer, KV head) times the shares of whichever kernel it takes.
+size_t part_rows(int64_t n_tok, int32_t B, int32_t max_seqlen, int32_t L, int32_t Hq, int32_t Hkv, int32_t dh,
+                 bool f32, bool with_lse);
+
 // Query heads of one KV group are split over `nsplit` pass-2 workgroups when the grid would
 // otherwise be small: the smallest divisor of G = Hq / Hkv that gives at least four workgroups per
 // compute unit (else G, one head each).  The fp32 kernels keep one workgroup per group.
@@ -79,21 +85,6 @@ inline int colsum_split(int64_t n_tok, int32_t B, int32_t max_seqlen, int32_t L,
     if (G % d == 0 && base * size_t(d) >= size_t(4) * n_cu) return d;
   return G;
 }
-
-// Rows of DH bf16 staged in LDS: 16-byte chunks XOR-swizzled so that 16
-// consecutive rows read at one logical chunk hit 16 distinct bank groups.
-template <int DH>
-struct RowTile {
-  static constexpr int kRowBytes = DH * 2;
-  static constexpr int kChunks = kRowBytes / 16;
-  static constexpr int kRowsPerInst = 64 / kChunks;  // rows one wave-wide 16-byte transfer fills
-  static constexpr int kRowsPerWindow = kRowBytes >= 256 ? 1 : 256 / kRowBytes;
-  __device__ static __forceinline__ int swz(int row, int chunk) {
-    return chunk ^ ((row / kRowsPerWindow) & (kChunks - 1));
-  }
-  // byte offset of the fragment (row, logical chunk)
-  __device__ static __forceinline__ int off(int row, int chunk) { return row * kRowBytes + swz(row, chunk) * 16; }
-};
 
 // Wave-cooperative staging of `rows` rows into LDS at `dst`; tile row r comes
 // from `src_row(r)`.  Waves take groups of kRowsPerInst rows round-robin.
@@ -480,23 +471,37 @@ struct LayerWeights {
   float w[kMaxWeightedLayers];
 };
 
-// S_j = (sum over layers l and the column-mass rows of each layer (KV heads, or shares of their
-// query heads) of w_l times the column masses) / (N * Hq); `Hkv` here counts those rows per layer
+// S_j = (sum over layers l and the `rows` column-mass rows of each layer (KV heads, or shares of their
+// query heads and row blocks) of w_l times the column masses) / (N * Hq).  A workgroup takes 64 tokens;
+// its four waves add rows q, q + 4, ..., eight loads in flight, and their sums are added in wave order
+// (one thread per token on one row at a time: 15 us for 32 x 2048 tokens and 32 rows, 10 us for one prompt
+// of 61 tokens on MI355X; so, 12.9 us with 256 rows and 4.5 us).
 __global__ __launch_bounds__(256) void attn_reduce_kernel(const float* __restrict__ part, const int* __restrict__ cu,
-                                                          int n_tok, int L, int Hkv, int Hq, int weighted,
+                                                          int n_tok, int L, int rows, int Hq, int weighted,
                                                           LayerWeights lw, float* __restrict__ S) {
+  __shared__ float red[4][64];
   const int b = blockIdx.y;
   const int base = cu[b];
   const int N = cu[b + 1] - base;
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= N) return;
-  float v = 0.f;
-  for (int l = 0; l < L; ++l) {
-    float vl = 0.f;
-    for (int g = 0; g < Hkv; ++g) vl += part[(size_t(l) * Hkv + g) * n_tok + base + j];
-    v = weighted ? fmaf(lw.w[l], vl, v) : v + vl;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int64_t j0 = int64_t(blockIdx.x) * 64; j0 < N; j0 += int64_t(gridDim.x) * 64) {
+    const int j = int(j0) + lane;
+    float v = 0.f;
+    if (j < N) {
+      for (int l = 0; l < L; ++l) {
+        const float* p = part + size_t(l) * rows * n_tok + base + j;
+        float vl = 0.f;
+#pragma unroll 8
+        for (int g = wave; g < rows; g += 4) vl += p[size_t(g) * n_tok];
+        v = weighted ? fmaf(lw.w[l], vl, v) : v + vl;
+      }
+    }
+    red[wave][lane] = v;
+    __syncthreads();
+    if (wave == 0 && j < N)
+      S[base + j] = ((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane])) / (float(N) * float(Hq));
+    __syncthreads();
   }
-  S[base + j] = v / (float(N) * float(Hq));
 }
 
 // The definition block_list_kernel follows, on the host (debug checks): (prompt, block) for
@@ -511,16 +516,24 @@ std::vector<int2> block_list_on_host(const std::vector<int>& cu, int B, int nblk
   return out;
 }
 
+size_t part_rows(int64_t n_tok, int32_t B, int32_t max_seqlen, int32_t L, int32_t Hq, int32_t Hkv, int32_t dh,
+                 bool f32, bool with_lse) {
+  const OnepassPlan one = plan_onepass(n_tok, B, max_seqlen, L, Hq, Hkv, dh, f32, with_lse);
+  const int shares = one.waves ? one.hsplit * one.rsplit : colsum_split(n_tok, B, max_seqlen, L, Hq, Hkv, f32);
+  return size_t(L) * Hkv * shares;
+}
+
 template <int DH>
 int launch(const char* fn, const void* Qv, const void* Kv, bool f32, const int* cu, int B, int max_seqlen, int n_tok,
            int L, int Hq, int Hkv, float scale, const float* lse_in, int strict, const float* layer_weights, float* S,
            float* lse2, float* part, int2* blist, hipStream_t s) {
   const int nsplit = colsum_split(n_tok, B, max_seqlen, L, Hq, Hkv, f32);  // part holds L * Hkv * nsplit rows
+  const OnepassPlan one = plan_onepass(n_tok, B, max_seqlen, L, Hq, Hkv, DH, f32, lse_in != nullptr);
   static_assert(kQBlock == kKBlock, "the two passes share one list of 256-row blocks");
   const float c2 = scale * kLog2e;
   const int nqb = (max_seqlen + kQBlock - 1) / kQBlock;
   const size_t n_bound = block_bound(n_tok, B, max_seqlen);
-  const bool use_list = use_block_list(n_tok, B, max_seqlen);
+  const bool use_list = one.waves == 0 && use_block_list(n_tok, B, max_seqlen);
   if (debug_checks_enabled()) {  // cu_seqlens before any kernel reads it
     std::vector<int> cu_h;
     const int st = debug_check_cu(fn, cu, B, n_tok, max_seqlen, s, &cu_h);
@@ -541,7 +554,12 @@ int launch(const char* fn, const void* Qv, const void* Kv, bool f32, const int* 
     lse2 = const_cast<float*>(lse_in);
     lse_mul = kLog2e;
   }
-  if (f32) {
+  int rows = Hkv * nsplit;  // column-mass rows per layer
+  if (one.waves) {
+    rows = Hkv * one.hsplit * one.rsplit;
+    launch_onepass(one, DH, static_cast<const uint16_t*>(Qv), static_cast<const uint16_t*>(Kv), cu, B, n_tok, L, Hq,
+                   Hkv, c2, strict, part, s);
+  } else if (f32) {
     launch_importance_f32(DH, static_cast<const float*>(Qv), static_cast<const float*>(Kv), cu, B, n_tok, L, Hq, Hkv,
                           nqb, c2, bl, n_rows, int(n_bound), lse_in == nullptr, lse2, lse_mul, strict, part, s);
   } else {
@@ -560,8 +578,8 @@ int launch(const char* fn, const void* Qv, const void* Kv, bool f32, const int* 
   LayerWeights lw{};
   if (layer_weights)
     for (int l = 0; l < L; ++l) lw.w[l] = layer_weights[l];
-  attn_reduce_kernel<<<dim3((max_seqlen + 255) / 256, B), dim3(256), 0, s>>>(part, cu, n_tok, L, Hkv * nsplit, Hq,
-                                                                             layer_weights ? 1 : 0, lw, S);
+  const unsigned reduce_x = unsigned(std::min<int64_t>((int64_t(max_seqlen) + 63) / 64, 65536));
+  attn_reduce_kernel<<<dim3(reduce_x, B), dim3(256), 0, s>>>(part, cu, n_tok, L, rows, Hq, layer_weights ? 1 : 0, lw, S);
   ESTP_CHECK_LAUNCH(fn);
   return ESTP_OK;
 }
@@ -618,12 +636,10 @@ int launch_dh(const char* fn, int dh, const void* q, const void* k, bool f32, co
 
 extern "C" size_t estp_attn_importance_workspace_size(int64_t n_tok, int32_t B, int32_t max_seqlen, int32_t L,
                                                       int32_t Hq, int32_t Hkv, int32_t dh, int dtype) {
-  (void)dh;
   if (n_tok < 1 || B < 1 || max_seqlen < 1 || L < 1 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0) return 0;
   Carver c(nullptr);
   c.take<float>(size_t(L) * Hq * n_tok);   // lse2 [L, Hq, n_tok]
-  c.take<float>(size_t(L) * Hkv * colsum_split(n_tok, B, max_seqlen, L, Hq, Hkv, dtype == ESTP_F32) *
-                n_tok);  // column masses [L, Hkv * nsplit, n_tok]
+  c.take<float>(part_rows(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype == ESTP_F32, false) * n_tok);
   c.take<int2>(block_bound(n_tok, B, max_seqlen));  // list of live 256-row blocks
   return c.bytes();
 }
@@ -644,8 +660,8 @@ extern "C" int estp_attn_importance(const void* Q, const void* K, const int32_t*
 
   Carver c(workspace);
   float* lse2 = c.take<float>(size_t(L) * Hq * n_tok);
-  float* part = c.take<float>(size_t(L) * Hkv * colsum_split(n_tok, B, max_seqlen, L, Hq, Hkv, dtype == ESTP_F32) *
-                              n_tok);
+  float* part =
+      c.take<float>(part_rows(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype == ESTP_F32, false) * n_tok);
   int2* blist = c.take<int2>(block_bound(n_tok, B, max_seqlen));
   return launch_dh("estp_attn_importance", dh, Q, K, dtype == ESTP_F32, cu_seqlens, B, max_seqlen, int(n_tok), L, Hq,
                    Hkv, scale, nullptr, 0, nullptr, S, lse2, part, blist, static_cast<hipStream_t>(stream));
@@ -654,11 +670,9 @@ extern "C" int estp_attn_importance(const void* Q, const void* K, const int32_t*
 extern "C" size_t estp_attn_importance_from_lse_workspace_size(int64_t n_tok, int32_t B, int32_t max_seqlen,
                                                                int32_t L, int32_t Hq, int32_t Hkv, int32_t dh,
                                                                int dtype) {
-  (void)dh;
   if (n_tok < 1 || B < 1 || max_seqlen < 1 || L < 1 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0) return 0;
   Carver c(nullptr);
-  c.take<float>(size_t(L) * Hkv * colsum_split(n_tok, B, max_seqlen, L, Hq, Hkv, dtype == ESTP_F32) *
-                n_tok);  // column masses [L, Hkv * nsplit, n_tok]
+  c.take<float>(part_rows(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype == ESTP_F32, true) * n_tok);
   c.take<int2>(block_bound(n_tok, B, max_seqlen));  // list of live 256-row blocks
   return c.bytes();
 }
@@ -679,8 +693,8 @@ extern "C" int estp_attn_importance_from_lse(const void* Q, const void* K, const
                "estp_attn_importance_from_lse: workspace must be non-null and 256-byte aligned");
 
   Carver c(workspace);
-  float* part = c.take<float>(size_t(L) * Hkv * colsum_split(n_tok, B, max_seqlen, L, Hq, Hkv, dtype == ESTP_F32) *
-                              n_tok);
+  float* part =
+      c.take<float>(part_rows(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype == ESTP_F32, true) * n_tok);
   int2* blist = c.take<int2>(block_bound(n_tok, B, max_seqlen));
   return launch_dh("estp_attn_importance_from_lse", dh, Q, K, dtype == ESTP_F32, cu_seqlens, B, max_seqlen,
                    int(n_tok), L, Hq, Hkv, scale, lse, 0, nullptr, S, nullptr, part, blist,
@@ -718,8 +732,8 @@ extern "C" int estp_attn_importance_ex(const void* Q, const void* K, const float
                "estp_attn_importance_ex: workspace must be non-null and 256-byte aligned");
   Carver c(workspace);
   float* lse2 = lse ? nullptr : c.take<float>(size_t(L) * Hq * n_tok);
-  float* part = c.take<float>(size_t(L) * Hkv * colsum_split(n_tok, B, max_seqlen, L, Hq, Hkv, dtype == ESTP_F32) *
-                              n_tok);
+  float* part =
+      c.take<float>(part_rows(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype == ESTP_F32, lse != nullptr) * n_tok);
   int2* blist = c.take<int2>(block_bound(n_tok, B, max_seqlen));
   return launch_dh("estp_attn_importance_ex", dh, Q, K, dtype == ESTP_F32, cu_seqlens, B, max_seqlen, int(n_tok), L,
                    Hq, Hkv, scale, lse, (flags & ESTP_IMPORTANCE_EXCLUDE_SELF) ? 1 : 0, layer_weights, S, lse2, part,

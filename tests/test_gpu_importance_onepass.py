@@ -1,0 +1,96 @@
+"""Importance of prompts of up to 2048 tokens in one pass, at the edges of its blocks, waves and shares, and
+where a row block has to be formed again with exact maxima, against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2608_15592_amd as estp
+from synth import inputs as I
+from tests._util import dev, host
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -24
+
+
+def _qk(lengths, L, Hq, Hkv, dh, seed, qscale=1.0):
+    g = np.random.default_rng(seed)
+    n = sum(lengths)
+    Q = I.f32_to_bf16_bits(qscale * g.standard_normal((L, n, Hq, dh)).astype(np.float32))
+    K = I.f32_to_bf16_bits(g.standard_normal((L, n, Hkv, dh)).astype(np.float32))
+    return Q, K, I.cu_seqlens_from_lengths(lengths)
+
+
+def _rtol(Q, K, scale, n_max):
+    """Relative bound on S: a score is within gamma_(dh + 1) of the sum of its products' sizes (at most
+    |q||k|), a probability within exp(2 delta) - 1 of its value, and sums of positive terms add an ulp a term."""
+    q = np.linalg.norm(oracle.widen(Q), axis=-1).max()
+    k = np.linalg.norm(oracle.widen(K), axis=-1).max()
+    delta = (Q.shape[-1] + 1) * U * scale * q * k
+    return np.expm1(2 * delta) + (n_max + 64) * U
+
+
+CASES = [
+    # lengths, L, Hq, Hkv, dh
+    ([1], 1, 4, 1, 128),
+    ([31, 32, 33], 1, 4, 2, 32),
+    ([255, 256, 257], 2, 2, 2, 64),       # eight row blocks and one past, a head of its own per KV head
+    ([1024], 1, 4, 1, 128),               # the most of four waves
+    ([1025], 1, 3, 1, 64),                # the least of eight
+    ([2048], 1, 2, 1, 128),               # the most of eight
+    ([2048, 1500, 1170], 1, 1, 1, 32),
+    ([40, 900, 3, 64, 129, 512, 7], 1, 6, 2, 128),  # a small ragged batch
+]
+
+
+@pytest.mark.parametrize("lengths,L,Hq,Hkv,dh", CASES, ids=["-".join(map(str, c[0])) + f"-dh{c[4]}" for c in CASES])
+def test_onepass_parity(lengths, L, Hq, Hkv, dh):
+    Q, K, cu = _qk(lengths, L, Hq, Hkv, dh, 3)
+    Qd, Kd, cud = dev(Q), dev(K), dev(cu)
+    rtol = _rtol(Q, K, dh ** -0.5, max(lengths))
+    S = estp.attn_importance(Qd, Kd, cud, max(lengths))
+    ref = oracle.attn_importance(Q, K, cu)
+    print(f"max rel |dS| / bound = {(np.abs(host(S) - ref) / ref / rtol).max():.3g}")
+    assert np.all(np.abs(host(S) - ref) <= rtol * ref)
+    assert torch.equal(S, estp.attn_importance(Qd, Kd, cud, max(lengths)))
+    # the general kernels on the same call (a bound on the lengths past the one pass)
+    if sum(lengths) >= 2049:
+        S2 = estp.attn_importance(Qd, Kd, cud, 2049)
+        assert np.all(np.abs(host(S2) - host(S)) <= 2 * rtol * ref)
+    # layer weights and the diagonal left out; the first token of a one-token prompt then gets exactly 0
+    w = [0.5 + l for l in range(L)]
+    S = host(estp.attn_importance_ex(Qd, Kd, cud, max(lengths), layer_weights=w, exclude_self=True))
+    ref = oracle.attn_importance(Q, K, cu, layer_weights=w, exclude_self=True)
+    assert np.all(np.abs(S - ref) <= rtol * np.abs(ref) + 2.0 ** -126)
+
+
+@pytest.mark.parametrize("tag", ["sharp", "all-low", "some-rows"])
+def test_onepass_sums_out_of_range(tag):
+    lengths, dh = [300, 70], 64
+    Q, K, cu = _qk(lengths, 1, 4, 2, dh, 4, qscale=40.0 if tag != "all-low" else 1.0)
+    if tag == "all-low":  # every score near -250 nats: the sums underflow
+        g = np.random.default_rng(5)
+        v = np.sign(g.standard_normal(dh)).astype(np.float32)
+        Q = I.f32_to_bf16_bits(6 * np.broadcast_to(v, Q.shape).astype(np.float32) + I.bf16_bits_to_f32(Q) * 0.1)
+        K = I.f32_to_bf16_bits(-6 * np.broadcast_to(v, K.shape).astype(np.float32) + I.bf16_bits_to_f32(K) * 0.1)
+    elif tag == "some-rows":
+        q = I.bf16_bits_to_f32(Q)
+        q[:, np.arange(q.shape[1]) % 7 != 0] /= 40.0
+        Q = I.f32_to_bf16_bits(q)
+    S = host(estp.attn_importance(dev(Q), dev(K), dev(cu), max(lengths)))
+    ref = oracle.attn_importance(Q, K, cu)
+    rtol = _rtol(Q, K, dh ** -0.5, max(lengths))
+    print(f"{tag}: bound {rtol:.2e}, max rel |dS| / bound = {(np.abs(S - ref) / ref / rtol).max():.3g}")
+    assert np.all(np.abs(S - ref) <= rtol * ref + 2.0 ** -126)
+
+
+def test_onepass_not_a_number_stays_in_its_rows():
+    # a query that is not a number reaches the keys up to its own token, as in the two-pass kernels
+    lengths, dh = [200], 64
+    Q, K, cu = _qk(lengths, 1, 2, 1, dh, 6)
+    q = I.bf16_bits_to_f32(Q)
+    q[0, 70, 1] = np.nan
+    S = host(estp.attn_importance(dev(I.f32_to_bf16_bits(q)), dev(K), dev(cu), 200))
+    assert np.all(np.isnan(S[:71]))
+    assert np.all(np.isfinite(S[71:]))
