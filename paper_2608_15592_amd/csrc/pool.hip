@@ -165,13 +165,19 @@ __global__ __launch_bounds__(1024) void minmax_stats_kernel(const float* __restr
   }
 }
 
-// One row's 8 consecutive features as loaded (raw), and their fp32 values.
+// One row's 8 consecutive features as loaded (raw), and their fp32 values.  kStream: non-temporal loads,
+// for bf16 rows that no cache will hold (stream_loads).
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 template <typename T>
 struct Row8;
 template <>
 struct Row8<uint16_t> {  // 8 bf16 in one 16-byte load
   using Raw = uint4;
-  __device__ static __forceinline__ Raw load(const uint16_t* p) { return *reinterpret_cast<const uint4*>(p); }
+  template <bool kStream>
+  __device__ static __forceinline__ Raw load(const uint16_t* p) {
+    if (kStream) return __builtin_bit_cast(Raw, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p)));
+    return *reinterpret_cast<const uint4*>(p);
+  }
   __device__ static __forceinline__ void fma8(float w, const Raw& q, float (&acc)[8]) {
     const uint32_t x[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
@@ -186,7 +192,9 @@ struct Row8<float> {  // 8 fp32 in two 16-byte loads
   struct Raw {
     float4 a, b;
   };
+  template <bool kStream>
   __device__ static __forceinline__ Raw load(const float* p) {
+    static_assert(!kStream, "two loads share a line");
     return Raw{*reinterpret_cast<const float4*>(p), *reinterpret_cast<const float4*>(p + 4)};
   }
   __device__ static __forceinline__ void fma8(float w, const Raw& q, float (&acc)[8]) {
@@ -209,7 +217,7 @@ __device__ __forceinline__ float fused_score(const float4& cf, float s, float h)
 // Streams one chunk of X.  Every wave forms the chunk's weights by itself
 // (wave reductions only, no workgroup barrier), so the first rows of X, which
 // do not depend on the weights, are already in flight while they are formed.
-template <typename T>
+template <typename T, bool kStream>
 __global__ __launch_bounds__(kThreads) void pool_partial_kernel(const T* __restrict__ X, const float* __restrict__ S,
                                                                 const float* __restrict__ H,
                                                                 const int* __restrict__ cu, int d, int n_chunk_max,
@@ -252,7 +260,7 @@ __global__ __launch_bounds__(kThreads) void pool_partial_kernel(const T* __restr
   if (active) {
 #pragma unroll
     for (int k = 0; k < kInFlight; ++k)
-      if (k < n_first) v[k] = Row8<T>::load(xp + size_t(k) * d);
+      if (k < n_first) v[k] = Row8<T>::template load<kStream>(xp + size_t(k) * d);
   }
 
   // u for rows lane, lane + 64, ...; wave-wide max (first arg-max), weights, sum
@@ -301,11 +309,11 @@ __global__ __launch_bounds__(kThreads) void pool_partial_kernel(const T* __restr
   int r = n_first;
   for (; r + kInFlight <= nr; r += kInFlight) {
 #pragma unroll
-    for (int k = 0; k < kInFlight; ++k) v[k] = Row8<T>::load(xp + size_t(r + k) * d);
+    for (int k = 0; k < kInFlight; ++k) v[k] = Row8<T>::template load<kStream>(xp + size_t(r + k) * d);
 #pragma unroll
     for (int k = 0; k < kInFlight; ++k) Row8<T>::fma8(w[r + k], v[k], acc);
   }
-  for (; r < nr; ++r) Row8<T>::fma8(w[r], Row8<T>::load(xp + size_t(r) * d), acc);
+  for (; r < nr; ++r) Row8<T>::fma8(w[r], Row8<T>::template load<kStream>(xp + size_t(r) * d), acc);
   float* out = part + (size_t(b) * n_chunk_max + chunk) * d + c;
   *reinterpret_cast<float4*>(out) = make_float4(acc[0], acc[1], acc[2], acc[3]);
   *reinterpret_cast<float4*>(out + 4) = make_float4(acc[4], acc[5], acc[6], acc[7]);
@@ -324,7 +332,7 @@ constexpr int kPromptWaves = kPromptThreads / 64;
 constexpr int kPromptSlice = 512;     // hidden features per workgroup: 8 per lane
 constexpr int kPromptMaxRows = 8192;  // weights of the prompt staged in LDS (32 KB)
 
-template <typename T>
+template <typename T, bool kStream>
 __global__ __launch_bounds__(kPromptThreads) void pool_prompt_kernel(
     const T* __restrict__ X, const float* __restrict__ S, const float* __restrict__ H, const int* __restrict__ cu,
     int d, int nslices, float a1, float a2, const float4* __restrict__ coef, float* __restrict__ pooled,
@@ -350,7 +358,7 @@ __global__ __launch_bounds__(kPromptThreads) void pool_prompt_kernel(
   if (active) {
 #pragma unroll
     for (int k = 0; k < kInFlight; ++k)
-      if (k < n_first) v[k] = Row8<T>::load(xp + size_t(wave + kPromptWaves * k) * d);
+      if (k < n_first) v[k] = Row8<T>::template load<kStream>(xp + size_t(wave + kPromptWaves * k) * d);
   }
 
   // u = c1 (S - centre_S) + c2 (H - centre_H) for every token of the prompt, the first arg-max, the exp-sum
@@ -389,11 +397,11 @@ __global__ __launch_bounds__(kPromptThreads) void pool_prompt_kernel(
     int q = n_first;
     for (; q + kInFlight <= nw; q += kInFlight) {
 #pragma unroll
-      for (int k = 0; k < kInFlight; ++k) v[k] = Row8<T>::load(xp + size_t(wave + kPromptWaves * (q + k)) * d);
+      for (int k = 0; k < kInFlight; ++k) v[k] = Row8<T>::template load<kStream>(xp + size_t(wave + kPromptWaves * (q + k)) * d);
 #pragma unroll
       for (int k = 0; k < kInFlight; ++k) Row8<T>::fma8(w[kPromptWaves * (q + k)], v[k], acc);
     }
-    for (; q < nw; ++q) Row8<T>::fma8(w[kPromptWaves * q], Row8<T>::load(xp + size_t(wave + kPromptWaves * q) * d), acc);
+    for (; q < nw; ++q) Row8<T>::fma8(w[kPromptWaves * q], Row8<T>::template load<kStream>(xp + size_t(wave + kPromptWaves * q) * d), acc);
   }
   float* rw = &red[wave][lane * 8];
   *reinterpret_cast<float4*>(rw) = make_float4(acc[0], acc[1], acc[2], acc[3]);
@@ -457,7 +465,7 @@ __host__ __device__ __forceinline__ int ragged_slices(int n, int d, int elem_byt
   return (d + w - 1) / w;
 }
 
-template <typename T>
+template <typename T, bool kStream>
 __global__ __launch_bounds__(kRaggedThreads) void pool_ragged_kernel(
     const T* __restrict__ X, const float* __restrict__ S, const float* __restrict__ H, const int* __restrict__ cu,
     int B, int d, size_t unit_bytes, float a1, float a2, const float4* __restrict__ coef,
@@ -521,7 +529,7 @@ __global__ __launch_bounds__(kRaggedThreads) void pool_ragged_kernel(
   const int n_first = min(nr, kInFlight);
 #pragma unroll
   for (int q = 0; q < kInFlight; ++q)
-    if (q < n_first) v[q] = Row8<T>::load(xp + size_t(rgrp + RP * q) * d);
+    if (q < n_first) v[q] = Row8<T>::template load<kStream>(xp + size_t(rgrp + RP * q) * d);
 
   // ---- the prompt's weights: u into LDS, first arg-max, exp-sum
   const float4 cf = coef_of(coef, b, a1, a2);
@@ -559,11 +567,11 @@ __global__ __launch_bounds__(kRaggedThreads) void pool_ragged_kernel(
   int q = n_first;
   for (; q + kInFlight <= nr; q += kInFlight) {
 #pragma unroll
-    for (int k = 0; k < kInFlight; ++k) v[k] = Row8<T>::load(xp + size_t(rgrp + RP * (q + k)) * d);
+    for (int k = 0; k < kInFlight; ++k) v[k] = Row8<T>::template load<kStream>(xp + size_t(rgrp + RP * (q + k)) * d);
 #pragma unroll
     for (int k = 0; k < kInFlight; ++k) Row8<T>::fma8(w[RP * (q + k)], v[k], acc);
   }
-  for (; q < nr; ++q) Row8<T>::fma8(w[RP * q], Row8<T>::load(xp + size_t(rgrp + RP * q) * d), acc);
+  for (; q < nr; ++q) Row8<T>::fma8(w[RP * q], Row8<T>::template load<kStream>(xp + size_t(rgrp + RP * q) * d), acc);
 
   // ---- add the RP row groups of each feature in a fixed order
   float* rw = red + tid * 8;
@@ -729,6 +737,15 @@ bool use_prompt_path(int64_t n_tok, int32_t B, int32_t max_seqlen, int32_t d) {
   const size_t wg = size_t(B) * ((size_t(d) + kPromptSlice - 1) / kPromptSlice);
   return wg >= size_t(n_cu) && (wg % size_t(n_cu) == 0 || wg >= 4 * size_t(n_cu));
 }
+// Whether X is read with non-temporal loads: bf16, and clearly larger than the 256 MB last-level cache, so
+// that its lines would only push each other out.  us per call on MI355X, plain and non-temporal: 1.76 GB
+// ragged 326 and 298, 537 MB 104 and 94 (two prompts of 32768 tokens 138 and 121), 470 MB 100 and 89, 369 MB
+// 76 and 69, 302 MB 66 and 67, 268 MB 56 and 61, 134 MB 57 and 61; fp32 rows, two loads to a line, 400 MB 80
+// and 89.
+bool stream_loads(int64_t n_tok, int32_t d, int dtype) {
+  return dtype == ESTP_BF16 && size_t(n_tok) * size_t(d) * 2 > (size_t(320) << 20);
+}
+
 // Prompts no longer than the LDS weight buffer, and few enough for the in-kernel scan: one kernel
 // with length-sized feature slices (pool_ragged_kernel) instead of chunk partials and a finisher.
 bool use_ragged_path(int32_t B, int32_t max_seqlen) {
@@ -830,16 +847,19 @@ extern "C" int estp_combine_pool(const void* X, const float* S, const float* H, 
     ESTP_CHECK_LAUNCH("minmax_stats_kernel");
     cf = coef;
   }
+  const bool stream_x = stream_loads(n_tok, d, dtype);
+  const uint16_t* xh = static_cast<const uint16_t*>(X);
+  const float* xf = static_cast<const float*>(X);
   if (use_prompt_path(n_tok, B, max_seqlen, d)) {
     const int ns = (d + kPromptSlice - 1) / kPromptSlice;
     const dim3 pgrid(unsigned(size_t(B) * ns));
-    if (dtype == ESTP_BF16) {
-      pool_prompt_kernel<uint16_t><<<pgrid, dim3(kPromptThreads), 0, s>>>(
-          static_cast<const uint16_t*>(X), S, H, cu_seqlens, int(d), ns, a1, a2, cf, pooled, e, top);
-    } else {
-      pool_prompt_kernel<float><<<pgrid, dim3(kPromptThreads), 0, s>>>(static_cast<const float*>(X), S, H, cu_seqlens,
-                                                                       int(d), ns, a1, a2, cf, pooled, e, top);
-    }
+    auto go = [&](auto kernel, auto x) {
+      kernel<<<pgrid, dim3(kPromptThreads), 0, s>>>(x, S, H, cu_seqlens, int(d), ns, a1, a2, cf, pooled, e, top);
+    };
+    if (dtype == ESTP_BF16)
+      stream_x ? go(pool_prompt_kernel<uint16_t, true>, xh) : go(pool_prompt_kernel<uint16_t, false>, xh);
+    else
+      go(pool_prompt_kernel<float, false>, xf);
     ESTP_CHECK_LAUNCH("pool_prompt_kernel");
     return ESTP_OK;
   }
@@ -849,13 +869,14 @@ extern "C" int estp_combine_pool(const void* X, const float* S, const float* H, 
     const size_t n_units = ragged_unit_bound(n_tok, B, d, esz, ub);
     ESTP_REQUIRE(fits_launch(n_units, kRaggedThreads), ESTP_ERR_UNSUPPORTED,
                  "estp_combine_pool: batch too large for one launch");
-    if (dtype == ESTP_BF16) {
-      pool_ragged_kernel<uint16_t><<<dim3(unsigned(n_units)), dim3(kRaggedThreads), 0, s>>>(
-          static_cast<const uint16_t*>(X), S, H, cu_seqlens, B, int(d), ub, a1, a2, cf, pooled, e, top);
-    } else {
-      pool_ragged_kernel<float><<<dim3(unsigned(n_units)), dim3(kRaggedThreads), 0, s>>>(
-          static_cast<const float*>(X), S, H, cu_seqlens, B, int(d), ub, a1, a2, cf, pooled, e, top);
-    }
+    auto go = [&](auto kernel, auto x) {
+      kernel<<<dim3(unsigned(n_units)), dim3(kRaggedThreads), 0, s>>>(x, S, H, cu_seqlens, B, int(d), ub, a1, a2, cf,
+                                                                      pooled, e, top);
+    };
+    if (dtype == ESTP_BF16)
+      stream_x ? go(pool_ragged_kernel<uint16_t, true>, xh) : go(pool_ragged_kernel<uint16_t, false>, xh);
+    else
+      go(pool_ragged_kernel<float, false>, xf);
     ESTP_CHECK_LAUNCH("pool_ragged_kernel");
     return ESTP_OK;
   }
@@ -874,13 +895,13 @@ extern "C" int estp_combine_pool(const void* X, const float* S, const float* H, 
   }
   const dim3 grid(unsigned(n_k * nslices));
   const int2* cmap = use_map ? map : nullptr;
-  if (dtype == ESTP_BF16) {
-    pool_partial_kernel<uint16_t><<<grid, dim3(kThreads), 0, s>>>(static_cast<const uint16_t*>(X), S, H, cu_seqlens,
-                                                                  int(d), nch, a1, a2, cf, part, cstat, nslices, cmap);
-  } else {
-    pool_partial_kernel<float><<<grid, dim3(kThreads), 0, s>>>(static_cast<const float*>(X), S, H, cu_seqlens, int(d),
-                                                               nch, a1, a2, cf, part, cstat, nslices, cmap);
-  }
+  auto go = [&](auto kernel, auto x) {
+    kernel<<<grid, dim3(kThreads), 0, s>>>(x, S, H, cu_seqlens, int(d), nch, a1, a2, cf, part, cstat, nslices, cmap);
+  };
+  if (dtype == ESTP_BF16)
+    stream_x ? go(pool_partial_kernel<uint16_t, true>, xh) : go(pool_partial_kernel<uint16_t, false>, xh);
+  else
+    go(pool_partial_kernel<float, false>, xf);
   ESTP_CHECK_LAUNCH("pool_partial_kernel");
   pool_finish_kernel<<<dim3(unsigned(size_t(n_finish) * B)), dim3(kThreads), 0, s>>>(
       part, cstat, S, H, cu_seqlens, int(d), nch, nslices, n_finish, a1, a2, cf, pooled, e, top);
