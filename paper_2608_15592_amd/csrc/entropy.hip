@@ -36,12 +36,13 @@
 //
 // Slices.  Token tiles in whole groups of 16 take 16 vocabulary slices: one
 // group is one workgroup on each of the 256 compute units.  The r < 16 tiles
-// left over (all of them, for a call of up to 3840 tokens) would leave most of
-// the chip idle at 16 slices (one tile: 16 workgroups), so their vocabulary is
-// cut into as many slices as give up to 256 workgroups (plan_slices).  ms per
-// call on MI355X at V 128256, d 4096, 16 slices and this: 61 tokens 2.19 and
-// 0.24, 719 tokens 2.25 and 0.57, 2048 tokens 2.29 and 1.43, 5000 tokens 5.4
-// and 3.5, 9000 tokens 8.4 and 6.4.
+// left over in a call of more than 2048 tokens would leave part of the chip
+// idle at 16 slices, so their vocabulary is cut into as many slices as give up
+// to 256 workgroups (plan_slices).  ms per call on MI355X at V 128256, d 4096,
+// 16 slices and this: 3000 tokens 2.49 and 2.12, 5000 5.4 and 3.5, 9000 8.4 and
+// 6.4.  Calls of up to 2048 tokens take entropy_few_kernel where it is faster,
+// which spreads the same 16 slices' arithmetic over 128 workgroups per 64
+// tokens, and otherwise the 16 slices.
 //
 // XCDs.  Workgroup ids are remapped so the 32 workgroups resident on one XCD
 // (ids are dealt round-robin over the 8 XCDs) cover 4 vocabulary slices x 8
@@ -109,6 +110,81 @@ __device__ __forceinline__ void arg_merge(float& av, int& ai, float bv, int bi) 
   ai = take ? bi : ai;
 }
 
+// Fold of a finished tile into one lane's running state of one token: the lane's 32 logits z(i, r) of
+// vocabulary rows 16 i + r past its first, live where 16 i + r < lim.
+//
+// The state (m, s, t) is kept relative to a reference m that is the running
+// log-sum-exp after each tile (rebased so that s = 1).  Full tiles are then
+// folded with 3 VALU ops and one exp2 per logit and no max pass; a tile whose
+// logits exceed the reference by more than 2^64 in weight (or overflow) is
+// refolded exactly with its own max.  The ragged last vocabulary tile always
+// takes the exact, masked path.
+template <typename Z>
+__device__ __forceinline__ Ent2 fold_tile(Ent2 e, bool first, bool ragged, int lim, Z&& z) {
+  bool exact = ragged;
+  if (!ragged) {
+    if (first) {  // first tile: the tile's own max is the reference
+      float mx = z(0, 0);
+#pragma unroll
+      for (int i = 0; i < kNB; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, z(i, r));
+      e = Ent2{mx * kLog2e, 0.f, 0.f};
+    }
+    float s = e.s, t = e.t;
+#pragma unroll
+    for (int i = 0; i < kNB; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float dd = fmaf(z(i, r), kLog2e, -e.m);
+        const float p = fast_exp2(dd);
+        s += p;
+        t = fmaf(p, dd, t);
+      }
+    if (s <= 0x1p64f) {
+      e.s = s;
+      e.t = t;
+    } else {
+      exact = true;  // overflow (or a logit far above the reference): refold exactly
+    }
+  }
+  if (exact) {
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < kNB; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const bool live = !ragged || i * 16 + r < lim;
+        mx = live ? fmaxf(mx, z(i, r)) : mx;
+      }
+    const float mnew = fmaxf(e.m, mx * kLog2e);
+    const float dl = fmaxf(e.m - mnew, kExp2Floor);
+    const float sc = fast_exp2(dl);
+    float s = sc * e.s;
+    float t = sc * (e.t + e.s * dl);
+#pragma unroll
+    for (int i = 0; i < kNB; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        // dead rows enter as -inf: dd clamps to the floor and adds 0 * floor,
+        // also while mnew is still -inf (a lane with no live row yet)
+        const bool live = !ragged || i * 16 + r < lim;
+        const float dd = fmaxf(fmaf(live ? z(i, r) : -INFINITY, kLog2e, -mnew), kExp2Floor);
+        const float p = fast_exp2(dd);
+        s += p;
+        t = fmaf(p, dd, t);
+      }
+    e = Ent2{mnew, s, t};
+  }
+  // rebase to the running log-sum-exp: m += log2 s, s = 1, t = t / s - log2 s
+  // (s >= 1 here: the reference never exceeds the largest logit seen, in base 2)
+  if (e.s > 0.f) {
+    const float dl = fast_log2(e.s);
+    e = Ent2{e.m + dl, 1.f, e.t / e.s - dl};
+  }
+  return e;
+}
+
 // How one call's token tiles are cut into workgroups.  The first main_tiles tiles (whole groups of
 // kGroupTiles) take kMaxVsplit vocabulary slices each, the rest tail_slices; the partial states are
 // [kMaxVsplit, main tokens] followed by [tail_slices, tail tokens].
@@ -118,37 +194,28 @@ struct SlicePlan {
   int tail_cols;  // token tiles of one slice that run next to each other on one XCD (0: plain order)
 };
 
-// Partial states per array that a call's workspace holds: kMaxVsplit per token and, while the
-// no-allocation entry point's fixed scratch has room for it, what kTailWgs workgroups of one token
-// tile each write.  Grows with n_tok, so a workspace sized for more tokens serves fewer.
+// Partial states per array that a call's workspace holds: one per token and slice (at most kMaxVsplit), or
+// entropy_few_kernel's 8 per token and slice, or, while the no-allocation entry point's fixed scratch has room
+// for it, also what kTailWgs workgroups of one token tile each write.  Grows with n_tok, so a workspace sized
+// for more tokens serves fewer.
 constexpr int64_t kTailMaxTok = 384 * kBT;
-constexpr int64_t kFineMaxTok = 4096;
+constexpr int64_t kFewMaxTok = 2048;
+inline int choose_vsplit(int n_vt) { return n_vt < kMaxVsplit ? n_vt : kMaxVsplit; }
 inline size_t partial_capacity(int64_t n_tok, int n_vt) {
-  if (n_vt <= kMaxVsplit) {
-    // fp32 calls of a few tokens over a small vocabulary cut it finer than 256 rows (f32_max_slices)
-    const size_t fine = size_t(n_tok < kFineMaxTok ? n_tok : kFineMaxTok) * kMaxVsplit;
-    const size_t plain = size_t(n_vt) * size_t(n_tok);
-    return plain > fine ? plain : fine;
+  const size_t slices = size_t(choose_vsplit(n_vt));
+  const size_t few = 8 * slices * size_t(n_tok < kFewMaxTok ? n_tok : kFewMaxTok);
+  size_t cap = slices * size_t(n_tok);
+  if (n_vt > kMaxVsplit) {
+    const size_t split = slices * size_t(n_tok < kTailMaxTok ? n_tok : kTailMaxTok) + size_t(kTailWgs) * kBT;
+    cap = cap > split ? cap : split;
   }
-  const size_t plain = size_t(kMaxVsplit) * size_t(n_tok);
-  const size_t capped = size_t(kMaxVsplit) * size_t(n_tok < kTailMaxTok ? n_tok : kTailMaxTok);
-  const size_t split = capped + size_t(kTailWgs) * kBT;
-  return plain > split ? plain : split;
-}
-
-// Most vocabulary slices of an fp32 call: as many as give its (64-token) tiles two workgroups per CU,
-// at least kMaxVsplit, and no more states than the workspace holds.
-inline int f32_max_slices(int64_t n_tok, int n_vt) {
-  if (n_vt < kMaxVsplit) return n_tok > kFineMaxTok ? n_vt : kMaxVsplit;
-  const int64_t want = 2 * kTailWgs / ((n_tok + 63) / 64), room = int64_t(partial_capacity(n_tok, n_vt)) / n_tok;
-  const int64_t most = want < room ? want : room;
-  return int(most > kMaxVsplit ? most : kMaxVsplit);
+  return cap > few ? cap : few;
 }
 
 // Slices of the n_tt token tiles.  With r tiles left over, tail_slices x r stays within kTailWgs
 // (one workgroup per CU), and among slice counts with the same largest number of vocabulary tiles
 // per workgroup the smallest is taken.  Vocabularies of up to kMaxVsplit tiles take one slice per
-// tile, and calls whose tail states would not fit the workspace kMaxVsplit.
+// tile; calls of up to kFewMaxTok tokens, and calls whose tail states would not fit the workspace, kMaxVsplit.
 inline SlicePlan plan_slices(int64_t n_tok, int n_vt) {
   const int n_tt = int((n_tok + kBT - 1) / kBT);
   SlicePlan p;
@@ -156,7 +223,7 @@ inline SlicePlan plan_slices(int64_t n_tok, int n_vt) {
   p.tail_slices = n_vt < kMaxVsplit ? n_vt : kMaxVsplit;
   p.tail_cols = 0;
   const int r = n_tt - p.main_tiles;
-  if (r > 0 && n_vt > kMaxVsplit) {
+  if (r > 0 && n_vt > kMaxVsplit && n_tok > kFewMaxTok) {
     const int most = kTailWgs / r < n_vt ? kTailWgs / r : n_vt;
     const int per_wg = (n_vt + most - 1) / most;
     const int slices = (n_vt + per_wg - 1) / per_wg;
@@ -246,13 +313,6 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
     }
   }
   const int nk = d / BK;
-  // Depth stage this workgroup starts every tile at (it wraps around).  A lone token tile streams
-  // W once, from HBM, with every workgroup on rows of its own: all at the same depth, their
-  // addresses differ by multiples of the row stride only and crowd on part of the memory channels
-  // (d 4096, V 128256, 256 tokens on MI355X: 320 us, with staggered starts 250).  With more tiles
-  // the workgroups of a slice share W, and those on one XCD the stages of X, through L2: staggered
-  // starts lose that (1024 tokens: 768 and 828 us), so they all start at 0.
-  const int ks0 = pl.main_tiles == 0 && pl.tail_cols == 1 ? (vs * 5) % nk : 0;
   const int n_my_tiles = (n_vt - vs + n_vsplit - 1) / n_vsplit;
   const size_t row_stride = size_t(d) * 2;  // bytes per row of W and X
 
@@ -277,7 +337,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
   // resource (no memory access, zeros into the slot being freed, never read),
   // so every barrier issues exactly 2 L transfers per wave and the waits below
   // are the same on every stage; the loop body stays one basic block.
-  int pf_tile = 0, pf_ks = ks0, pf_slot = 0, pf_op = 0;
+  int pf_tile = 0, pf_ks = 0, pf_slot = 0, pf_op = 0;
   int pf_vt = vs;                                                                  // vocabulary tile of the prefetch
   const char* pf_w = reinterpret_cast<const char*>(W) + size_t(vs) * tile_bytes;  // its rows of W
   const size_t w_step = size_t(n_vsplit) * tile_bytes;
@@ -299,8 +359,9 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
       p.rsrc = make_rsrc(pf_w, rows * uint32_t(row_stride));
     } else {
       p.rsrc = live ? rx : r_none;
-      pf_ks = pf_ks + 1 == nk ? 0 : pf_ks + 1;
-      if (pf_ks == ks0) {
+      const bool wrap = pf_ks + 1 == nk;
+      pf_ks = wrap ? 0 : pf_ks + 1;
+      if (wrap) {
         ++pf_tile;
         pf_vt += n_vsplit;
         pf_w += w_step;
@@ -437,82 +498,12 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
     // ---- fold the finished tile into the running states.  acc[i][j][r] is the
     // logit of vocabulary row vt*256 + wv*128 + 16 i + 4 fq + r for token
     // tt*256 + wt*128 + 16 j + fr.
-    //
-    // The state (m, s, t) is kept relative to a reference m that is the running
-    // log-sum-exp after each tile (rebased so that s = 1).  Full tiles are then
-    // folded with 3 VALU ops and one exp2 per logit and no max pass; a tile whose
-    // logits exceed the reference by more than 2^64 in weight (or overflow) is
-    // refolded exactly with its own max.  The ragged last vocabulary tile always
-    // takes the exact, masked path.
     const int vt = vs + tile * n_vsplit;
     const bool ragged = (vt + 1) * kBV > V;
     const int lim = V - (vt * kBV + wv * 128 + 4 * fq);  // live rows: 16 i + r < lim
 #pragma unroll
-    for (int j = 0; j < kNB; ++j) {
-      Ent2 e = st[j];
-      bool exact = ragged;
-      if (!ragged) {
-        if (tile == 0) {  // first tile: the tile's own max is the reference
-          float mx = acc[0][j][0];
-#pragma unroll
-          for (int i = 0; i < kNB; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, acc[i][j][r]);
-          e = Ent2{mx * kLog2e, 0.f, 0.f};
-        }
-        float s = e.s, t = e.t;
-#pragma unroll
-        for (int i = 0; i < kNB; ++i)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float dd = fmaf(acc[i][j][r], kLog2e, -e.m);
-            const float p = fast_exp2(dd);
-            s += p;
-            t = fmaf(p, dd, t);
-          }
-        if (s <= 0x1p64f) {
-          e.s = s;
-          e.t = t;
-        } else {
-          exact = true;  // overflow (or a logit far above the reference): refold exactly
-        }
-      }
-      if (exact) {
-        float mx = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < kNB; ++i)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const bool live = !ragged || i * 16 + r < lim;
-            mx = live ? fmaxf(mx, acc[i][j][r]) : mx;
-          }
-        const float mnew = fmaxf(e.m, mx * kLog2e);
-        const float dl = fmaxf(e.m - mnew, kExp2Floor);
-        const float sc = fast_exp2(dl);
-        float s = sc * e.s;
-        float t = sc * (e.t + e.s * dl);
-#pragma unroll
-        for (int i = 0; i < kNB; ++i)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            // dead rows enter as -inf: dd clamps to the floor and adds 0 * floor,
-            // also while mnew is still -inf (a lane with no live row yet)
-            const bool live = !ragged || i * 16 + r < lim;
-            const float dd = fmaxf(fmaf(live ? acc[i][j][r] : -INFINITY, kLog2e, -mnew), kExp2Floor);
-            const float p = fast_exp2(dd);
-            s += p;
-            t = fmaf(p, dd, t);
-          }
-        e = Ent2{mnew, s, t};
-      }
-      // rebase to the running log-sum-exp: m += log2 s, s = 1, t = t / s - log2 s
-      // (s >= 1 here: the reference never exceeds the largest logit seen, in base 2)
-      if (e.s > 0.f) {
-        const float dl = fast_log2(e.s);
-        e = Ent2{e.m + dl, 1.f, e.t / e.s - dl};
-      }
-      st[j] = e;
-    }
+    for (int j = 0; j < kNB; ++j)
+      st[j] = fold_tile(st[j], tile == 0, ragged, lim, [&](int i, int r) { return acc[i][j][r]; });
     if (kArg) {
       // the next-token mode, in a loop of its own so that the eight columns' independent compare
       // chains interleave.  Per column: the tile's largest live logit, then the lowest of the
@@ -627,6 +618,237 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
   }
 }
 
+// ------------------------------------------------------------------ few tokens
+//
+// entropy_few_kernel: calls of up to 2048 tokens, with the results of entropy_gemm_kernel at 16 slices bit
+// for bit.  There, one lane's state of a token follows the 32 vocabulary rows (half wv, row quad fq) of each
+// of its slice's tiles in turn, so the slice's 8 (wv, fq) states are independent until they merge.  Here a
+// workgroup takes ONE of them, (vs, wv, fq), for 64 tokens: 128 workgroups per 64 tokens instead of 16 per
+// 256.  It multiplies the state's rows of 8 of the slice's tiles at a time, 256 rows x 64 tokens over the full
+// depth in the same order of matrix-core steps; the logits go through LDS, four tiles at a time, to one wave
+// that folds them tile by tile, one token per lane, with the same fold.  entropy_few_merge_kernel merges the
+// states in the order the lanes, halves and slices do there.  Bound by the supply of W and X into LDS (40 KB
+// per 512 cycles of matrix-core work) and, for one block of tokens, by HBM.  us per call on MI355X at V 128256,
+// d 4096, 16 slices and this: @FEW@
+constexpr int kFewTok = 64;     // tokens per workgroup
+constexpr int kFewTiles = 8;    // vocabulary tiles per product
+constexpr int kFewRows = 32 * kFewTiles;
+constexpr int kFewRing = 3;     // LDS stages of 64 depths
+constexpr int kFewStage = (kFewRows + kFewTok) * 128;
+constexpr int kFewPitch = kFewTok + 4;  // logits of a row; the four row quads of a store land in distinct banks
+static_assert(kFewRows == 64 * kWaves, "two tiles per wave");
+
+template <bool kArg>
+__global__ __launch_bounds__(kWaves * 64, 1) void entropy_few_kernel(
+    const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int n_tok, int d, int V, int n_vsplit, int n_vt,
+    int n_tb, float* __restrict__ part_m, float* __restrict__ part_s, float* __restrict__ part_t,
+    float* __restrict__ part_zmax, int* __restrict__ part_arg) {
+  using G = Geom<64>;
+  __shared__ __attribute__((aligned(16))) char lds[kFewRing * kFewStage + 4 * 32 * kFewPitch * 4];
+  float* logits = reinterpret_cast<float*>(lds + kFewRing * kFewStage);  // [4 tiles][32 rows][kFewPitch]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // an eighth of the states to each XCD, the token blocks of a state next to each other (the same rows of W)
+  const int j = blockIdx.x >> 3, tb = j % n_tb;
+  const int state = (j / n_tb) * 8 + (blockIdx.x & 7);
+  const int sq = state & 3, wv = (state >> 2) & 1, vs = state >> 3;
+  const int nk = d / 64;
+  const int n_my = (n_vt - vs + n_vsplit - 1) / n_vsplit;  // tiles of the slice
+  const int n_groups = (n_my + kFewTiles - 1) / kFewTiles;
+  const uint32_t row_stride = uint32_t(d) * 2;
+
+  // staging: row m of the W part is row 4 sq + r of 16-row block i of half wv of tile m / 32 of the group,
+  // with i = m % 32 / 4 and r = m % 4; transfer q of a wave fills 8 rows (1 KB)
+  constexpr int LW = kFewRows / (8 * kWaves), LX = kFewTok / (8 * kWaves);
+  uint32_t w_off[LW], x_off[LX];
+#pragma unroll
+  for (int q = 0; q < LW; ++q) {
+    const int m = 8 * (kWaves * q + wave) + lane / 8;
+    const uint32_t row = uint32_t(m / 32) * uint32_t(n_vsplit) * kBV + wv * 128 + 16 * (m % 32 / 4) + 4 * sq + m % 4;
+    w_off[q] = row * row_stride + uint32_t(G::swz(m, lane % 8) * 16);
+  }
+#pragma unroll
+  for (int q = 0; q < LX; ++q) {
+    const int m = 8 * (kWaves * q + wave) + lane / 8;
+    x_off[q] = uint32_t(m) * row_stride + uint32_t(G::swz(m, lane % 8) * 16);
+  }
+  const buf_rsrc_t rx = make_rsrc(reinterpret_cast<const char*>(X) + size_t(tb) * kFewTok * row_stride,
+                                  uint32_t(min(kFewTok, n_tok - tb * kFewTok)) * row_stride);
+  int pf_g = 0, pf_ks = 0, pf_slot = 0;
+  auto issue_stage = [&]() {  // past the last group: empty resources, no access
+    const bool live = pf_g < n_groups;
+    const int64_t row0 = int64_t(vs + (live ? pf_g : 0) * kFewTiles * n_vsplit) * kBV;
+    const int64_t rows = min(int64_t(V) - row0, int64_t((kFewTiles - 1) * n_vsplit + 1) * kBV);
+    const buf_rsrc_t rw =
+        make_rsrc(reinterpret_cast<const char*>(W) + size_t(row0) * row_stride, live ? uint32_t(rows) * row_stride : 0u);
+    const buf_rsrc_t rxx = live ? rx : make_rsrc(X, 0u);
+    char* dst = lds + pf_slot * kFewStage + 1024 * wave;
+    const uint32_t soff = uint32_t(pf_ks) * 128u;
+#pragma unroll
+    for (int q = 0; q < LW; ++q) lds_dma16_buf(rw, w_off[q], soff, dst + 1024 * kWaves * q);
+#pragma unroll
+    for (int q = 0; q < LX; ++q) lds_dma16_buf(rxx, x_off[q], soff, dst + kFewRows * 128 + 1024 * kWaves * q);
+    pf_slot = pf_slot + 1 == kFewRing ? 0 : pf_slot + 1;
+    const bool wrap = pf_ks + 1 == nk;
+    pf_ks = wrap ? 0 : pf_ks + 1;
+    pf_g += wrap;
+  };
+  const int fr = lane & 15, fq = lane >> 4;
+  uint32_t a_off[2], b_off[2];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) {
+    a_off[kk] = (64 * wave + fr) * 128 + G::swz(fr, kk * 4 + fq) * 16;
+    b_off[kk] = (kFewRows + fr) * 128 + G::swz(fr, kk * 4 + fq) * 16;
+  }
+
+  Ent2 st{-INFINITY, 0.f, 0.f};  // wave 0, lane = token
+  float zmax = -INFINITY;
+  int zarg = INT32_MAX;
+  int slot = 0;
+#pragma unroll
+  for (int q = 0; q < kFewRing - 1; ++q) issue_stage();
+  for (int g = 0; g < n_groups; ++g) {
+    f32x4_t acc[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[a][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int ks = 0; ks < nk; ++ks) {
+      wait_vm<(kFewRing - 2) * (LW + LX)>();
+      lds_barrier();  // the stage is visible, and nobody reads the one before it any more
+      issue_stage();
+      const char* base = lds + slot * kFewStage;
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        bf16x8_t fa[4], fb[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          fa[q] = *reinterpret_cast<const bf16x8_t*>(base + a_off[kk] + q * 2048);
+          fb[q] = *reinterpret_cast<const bf16x8_t*>(base + b_off[kk] + q * 2048);
+        }
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) acc[a][b] = mfma16(fa[a], fb[b], acc[a][b]);
+      }
+      slot = slot + 1 == kFewRing ? 0 : slot + 1;
+    }
+    // acc[a][b][r]: tile 2 wave + a / 2 of the group, 16-row block i = 4 (a % 2) + fq, row r; token 16 b + fr
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      lds_barrier();  // the logits before these are folded
+      if ((wave >> 1) == c) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              logits[((2 * (wave & 1) + a / 2) * 32 + 4 * (4 * (a % 2) + fq) + r) * kFewPitch + 16 * b + fr] =
+                  acc[a][b][r];
+      }
+      lds_barrier();
+      if (wave == 0) {
+        for (int q = 0; q < 4; ++q) {
+          const int tile = kFewTiles * g + 4 * c + q;
+          if (tile >= n_my) break;
+          float z[kNB][4];
+#pragma unroll
+          for (int i = 0; i < kNB; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z[i][r] = logits[(q * 32 + 4 * i + r) * kFewPitch + lane];
+          const int vt = vs + tile * n_vsplit;
+          const bool ragged = (vt + 1) * kBV > V;
+          const int row0 = vt * kBV + wv * 128 + 4 * sq, lim = V - row0;
+          st = fold_tile(st, tile == 0, ragged, lim, [&](int i, int r) { return z[i][r]; });
+          if (kArg) {
+#pragma unroll
+            for (int i = 0; i < kNB; ++i)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {  // rows ascend: strict keeps the lowest among equal logits
+                const bool up = (!ragged | (i * 16 + r < lim)) & (z[i][r] > zmax);
+                zmax = up ? z[i][r] : zmax;
+                zarg = up ? row0 + i * 16 + r : zarg;
+              }
+          }
+        }
+      }
+    }
+  }
+  wait_vm<0>();  // no transfer into LDS outlives the workgroup
+  const int tok = tb * kFewTok + lane;
+  if (wave == 0 && tok < n_tok) {
+    const size_t o = size_t(state) * n_tok + tok;
+    part_m[o] = st.m;
+    part_s[o] = st.s;
+    part_t[o] = st.t;
+    if (kArg) {
+      part_zmax[o] = zmax;
+      part_arg[o] = zarg;
+    }
+  }
+}
+
+// Merge of entropy_few_kernel's 8 states per slice and token, in the order of entropy_gemm_kernel: row quads 0
+// with 1 and 2 with 3, those two, the halves, then the slices in turn.  16 tokens per workgroup, one thread
+// per (slice, token) for its 8 states, one per token for the slices.
+__global__ __launch_bounds__(256) void entropy_few_merge_kernel(const float* __restrict__ part_m,
+                                                                const float* __restrict__ part_s,
+                                                                const float* __restrict__ part_t,
+                                                                const float* __restrict__ part_zmax,
+                                                                const int* __restrict__ part_arg, int n_tok,
+                                                                int n_vsplit, float* __restrict__ H,
+                                                                int32_t* __restrict__ arg) {
+  __shared__ float sh[5][kMaxVsplit][16];
+  const int t = threadIdx.x & 15, vs = threadIdx.x >> 4, tok = blockIdx.x * 16 + t;
+  if (tok < n_tok && vs < n_vsplit) {
+    Ent2 p[8];
+    float zb = -INFINITY;
+    int ib = INT32_MAX;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const size_t o = size_t(8 * vs + q) * n_tok + tok;
+      p[q] = Ent2{part_m[o], part_s[o], part_t[o]};
+      if (arg) arg_merge(zb, ib, part_zmax[o], part_arg[o]);
+    }
+    Ent2 h[2];
+#pragma unroll
+    for (int w = 0; w < 2; ++w)
+      h[w] = ent2_merge(ent2_merge(p[4 * w], p[4 * w + 1]), ent2_merge(p[4 * w + 2], p[4 * w + 3]));
+    const Ent2 a = ent2_merge(h[0], h[1]);
+    sh[0][vs][t] = a.m;
+    sh[1][vs][t] = a.s;
+    sh[2][vs][t] = a.t;
+    sh[3][vs][t] = zb;
+    sh[4][vs][t] = __int_as_float(ib);
+  }
+  __syncthreads();
+  if (vs != 0 || tok >= n_tok) return;
+  Ent2 a{sh[0][0][t], sh[1][0][t], sh[2][0][t]};
+  float zb = sh[3][0][t];
+  int ib = __float_as_int(sh[4][0][t]);
+  for (int v = 1; v < n_vsplit; ++v) {
+    a = ent2_merge(a, Ent2{sh[0][v][t], sh[1][v][t], sh[2][v][t]});
+    arg_merge(zb, ib, sh[3][v][t], __float_as_int(sh[4][v][t]));
+  }
+  H[tok] = kLn2 * (fast_log2(a.s) - a.t / a.s);
+  if (arg) arg[tok] = ib;
+}
+
+// Whether a call takes entropy_few_kernel: an estimate of both kernels in thousands of cycles, rounds of
+// workgroups over the chip times a workgroup's stages and folds.
+inline bool use_few(int64_t n_tok, int d, int n_vt) {
+  const int slices = choose_vsplit(n_vt);
+  if (n_tok > kFewMaxTok || d % 64 != 0) return false;
+  if (size_t((kFewTiles - 1) * slices + 1) * kBV * size_t(d) * 2 >= (size_t(1) << 32)) return false;  // 32-bit offsets
+  const int nk = d / 64, tiles = (n_vt + slices - 1) / slices, groups = (tiles + kFewTiles - 1) / kFewTiles;
+  const int few_wgs = 8 * slices * int((n_tok + kFewTok - 1) / kFewTok);
+  const int gemm_wgs = slices * int((n_tok + kBT - 1) / kBT);
+  const float few = float((few_wgs + 255) / 256) * float(groups) * (0.9f * float(nk) + 8.5f);
+  const float gemm = float((gemm_wgs + 255) / 256) * float(tiles) * (2.05f * float(nk) + 8.f);
+  return few < 0.9f * gemm;
+}
+
 // Merge the partial states of each token and write H in nats: H = ln2 * (log2 s - t / s).  With
 // `arg` non-null, also the vocabulary index of the largest logit over the slices (lowest index
 // among equal maxima).  The tokens are first .. first + n, their states [n_slices, n].  kLanes
@@ -726,7 +948,7 @@ int check_entropy_args(const char* fn, const void* X, const void* W, int64_t n_t
                "%s: H and vocab_argmax must be 4-byte aligned", fn);
   const int n = int(n_tok);
   const int n_vt = (V + kBV - 1) / kBV;
-  const size_t n_wg = dtype == ESTP_F32 ? entropy_f32_workgroups(n, V, f32_max_slices(n, n_vt))
+  const size_t n_wg = dtype == ESTP_F32 ? entropy_f32_workgroups(n, choose_vsplit(n_vt))
                                         : plan_workgroups(plan_slices(n, n_vt), n);
   ESTP_REQUIRE(fits_launch(n_wg, kWaves * 64), ESTP_ERR_UNSUPPORTED,
                "%s: n_tok = %d needs %zu workgroups, more than one launch holds", fn, n, n_wg);
@@ -761,11 +983,22 @@ int launch_token_entropy(const void* X, const void* W, int n, int d, int V, int 
   };
 
   if (dtype == ESTP_F32) {
-    const int most = f32_max_slices(n, n_vt);
-    launch_entropy_f32(static_cast<const float*>(X), static_cast<const float*>(W), n, d, V, most, pm, ps, pt, pz,
+    const int n_vsplit = choose_vsplit(n_vt);
+    launch_entropy_f32(static_cast<const float*>(X), static_cast<const float*>(W), n, d, V, n_vsplit, pm, ps, pt, pz,
                        want_arg ? pa : nullptr, s);
     ESTP_CHECK_LAUNCH("entropy_f32_kernel");
-    merge(0, n, entropy_f32_slices(n, V, most), 0);
+    merge(0, n, n_vsplit, 0);
+  } else if (use_few(n, d, n_vt)) {
+    const int n_vsplit = choose_vsplit(n_vt), n_tb = (n + kFewTok - 1) / kFewTok;
+    const dim3 grid(unsigned(8 * n_vsplit * n_tb)), block(kWaves * 64);
+    auto go = [&](auto kernel) {
+      kernel<<<grid, block, 0, s>>>(static_cast<const uint16_t*>(X), static_cast<const uint16_t*>(W), n, d, V, n_vsplit,
+                                    n_vt, n_tb, pm, ps, pt, pz, pa);
+    };
+    want_arg ? go(entropy_few_kernel<true>) : go(entropy_few_kernel<false>);
+    ESTP_CHECK_LAUNCH("entropy_few_kernel");
+    entropy_few_merge_kernel<<<dim3((n + 15) / 16), dim3(256), 0, s>>>(pm, ps, pt, pz, pa, n, n_vsplit, H,
+                                                                       vocab_argmax);
   } else {
     const SlicePlan pl = plan_slices(n, n_vt);
     const dim3 grid(unsigned(plan_workgroups(pl, n))), block(kWaves * 64);

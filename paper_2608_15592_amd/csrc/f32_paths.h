@@ -11,14 +11,13 @@
 namespace estp {
 namespace detail {
 
-// Vocabulary slices that launch_entropy_f32 writes partial states for, at most max_slices, and the
-// workgroups in its grid.
-int entropy_f32_slices(int n_tok, int V, int max_slices);
-size_t entropy_f32_workgroups(int n_tok, int V, int max_slices);
-// Per-slice online-softmax partial states (part_m/s/t [slices, n_tok], base 2) of the logits W x for
-// every token.  With part_arg non-null, also each slice's largest logit (part_zmax) and its lowest
-// vocabulary index (part_arg), same layout.
-void launch_entropy_f32(const float* X, const float* W, int n_tok, int d, int V, int max_slices, float* part_m,
+// Workgroups in launch_entropy_f32's grid.
+size_t entropy_f32_workgroups(int n_tok, int n_vsplit);
+// Per-slice online-softmax partial states (part_m/s/t [n_vsplit, n_tok], base
+// 2) of the logits W x for every token; 1 <= n_vsplit <= ceil(V / 128).  With
+// part_arg non-null, also each slice's largest logit (part_zmax) and its
+// lowest vocabulary index (part_arg), same layout.
+void launch_entropy_f32(const float* X, const float* W, int n_tok, int d, int V, int n_vsplit, float* part_m,
                         float* part_s, float* part_t, float* part_zmax, int* part_arg, hipStream_t s);
 
 // The two importance passes over the same grid as the bf16 kernels: n_rows

@@ -11,9 +11,9 @@ from tests._util import check_vocab_argmax, dev, host, logit_error_bound
 
 # (n_tok, d, V): V in 256-row tiles, tokens in 256-token tiles
 CASES = [
-    (1, 64, 16400),      # one token: 65 tiles, one each
-    (256, 96, 70000),    # a lone tile, 274 vocabulary tiles: two per workgroup, 32-deep stages
-    (257, 64, 16400),    # two tiles, the second with one token
+    (1, 64, 16400),      # one token
+    (256, 96, 70000),    # 32-deep stages
+    (257, 64, 16400),
     (2304, 64, 8200),    # 9 tiles: two column groups of 5 and 4, 28 slices
     (3840, 32, 4353),    # 15 tiles, 17 slices, odd multiple of 32
     (4096, 64, 4353),    # one whole group, nothing past it
@@ -23,14 +23,12 @@ CASES = [
 ]
 
 
-# fp32: tiles of 64 x 64 (calls that 128 x 128 tiles would not spread over the chip) and of 128 x 128
 CASES_F32 = [
     (1, 8, 1),
     (63, 40, 65),        # depth ends inside a step
     (65, 72, 129),       # one token and one word past a tile
-    (129, 64, 16500),    # 170 slices
-    (4097, 32, 300),     # few vocabulary tiles: no more slices than 256-row tiles
-    (2100, 32, 33000),   # 128 x 128 tiles, ragged both ways
+    (129, 64, 16500),
+    (4097, 32, 300),     # few vocabulary tiles
 ]
 
 
@@ -73,6 +71,25 @@ def test_entropy_slices(n, d, V):
 def test_entropy_slices_f32(n, d, V):
     X, W = _inputs(n, d, V)
     _check(X, W, n, V)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,V", [(64, 33000), (192, 4097), (128, 40000), (64, 300)])
+def test_few_tokens_change_no_bit(d, V):
+    # a call of up to 2048 tokens spreads the same arithmetic over more workgroups: its rows of a call of
+    # one whole group of token tiles, bit for bit, with vocabularies of a ragged last tile, of tiles that
+    # do not fill the last product of a slice, and of fewer tiles than slices; at block edges of the tokens
+    X, W = _inputs(4096, d, V)
+    W[V // 2:] *= 40.0  # later tiles far above the running reference: folded exactly
+    Xd, Wd = dev(I.f32_to_bf16_bits(X)), dev(I.f32_to_bf16_bits(W))
+    am = torch.empty(4096, dtype=torch.int32, device="cuda")
+    H = estp.token_entropy(Xd, Wd, vocab_argmax=am)
+    for n in (1, 63, 64, 65, 200, 719, 2048):
+        x = Xd[:n].contiguous()
+        a = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+        assert torch.equal(estp.token_entropy(x, Wd, vocab_argmax=a), H[:n])
+        assert torch.equal(a, am[:n])
+        assert torch.equal(estp.token_entropy(x, Wd), H[:n])
 
 
 def test_entropy_workspace_grows_with_tokens():
