@@ -53,6 +53,7 @@
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "estp_common.h"
 #include "f32_paths.h"
@@ -626,26 +627,29 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
 // workgroup takes ONE of them, (vs, wv, fq), for 64 tokens: 128 workgroups per 64 tokens instead of 16 per
 // 256.  It multiplies the state's rows of 8 of the slice's tiles at a time, 256 rows x 64 tokens over the full
 // depth in the same order of matrix-core steps; the logits go through LDS, four tiles at a time, to one wave
-// that folds them tile by tile, one token per lane, with the same fold.  entropy_few_merge_kernel merges the
-// states in the order the lanes, halves and slices do there.  Bound by the supply of W and X into LDS (40 KB
-// per 512 cycles of matrix-core work) and, for one block of tokens, by HBM.  us per call on MI355X at V 128256,
-// d 4096, 16 slices and this: @FEW@
-constexpr int kFewTok = 64;     // tokens per workgroup
+// that folds them tile by tile, one token per lane, with the same fold (128 tokens a workgroup: one tile at a
+// time, two waves).  entropy_few_merge_kernel merges the states in the order the lanes, halves and slices do
+// there.  Bound by the supply of W and X into LDS (48 KB a stage, 25 B per cycle and CU as in the large
+// kernel, against 1024 cycles of matrix-core work) and, for one block of tokens, by HBM (4.2 TB/s).  us per
+// call on MI355X, 16 slices and this, V 128256, d 4096: 61 tokens 2190 and 266, 256 2285 and 316, 719 2260 and
+// 811, 1500 2270 and 1590; d 2048: 61 tokens 1177 and 145, 1024 1218 and 608.
 constexpr int kFewTiles = 8;    // vocabulary tiles per product
 constexpr int kFewRows = 32 * kFewTiles;
 constexpr int kFewRing = 3;     // LDS stages of 64 depths
-constexpr int kFewStage = (kFewRows + kFewTok) * 128;
-constexpr int kFewPitch = kFewTok + 4;  // logits of a row; the four row quads of a store land in distinct banks
 static_assert(kFewRows == 64 * kWaves, "two tiles per wave");
 
-template <bool kArg>
+template <int NT, bool kArg, bool kStreamW>
 __global__ __launch_bounds__(kWaves * 64, 1) void entropy_few_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int n_tok, int d, int V, int n_vsplit, int n_vt,
     int n_tb, float* __restrict__ part_m, float* __restrict__ part_s, float* __restrict__ part_t,
     float* __restrict__ part_zmax, int* __restrict__ part_arg) {
   using G = Geom<64>;
-  __shared__ __attribute__((aligned(16))) char lds[kFewRing * kFewStage + 4 * 32 * kFewPitch * 4];
-  float* logits = reinterpret_cast<float*>(lds + kFewRing * kFewStage);  // [4 tiles][32 rows][kFewPitch]
+  constexpr int NB = NT / 16;                  // token blocks, all of them in every wave
+  constexpr int kStage = (kFewRows + NT) * 128;
+  constexpr int CT = NT == 64 ? 4 : 1;         // tiles whose logits the LDS beside the ring holds
+  constexpr int kPitch = NT == 64 ? NT + 4 : NT;  // (with room, the row quads of a store land in distinct banks)
+  __shared__ __attribute__((aligned(16))) char lds[kFewRing * kStage + CT * 32 * kPitch * 4];
+  float* logits = reinterpret_cast<float*>(lds + kFewRing * kStage);  // [CT tiles][32 rows][kPitch]
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // an eighth of the states to each XCD, the token blocks of a state next to each other (the same rows of W)
@@ -659,7 +663,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_few_kernel(
 
   // staging: row m of the W part is row 4 sq + r of 16-row block i of half wv of tile m / 32 of the group,
   // with i = m % 32 / 4 and r = m % 4; transfer q of a wave fills 8 rows (1 KB)
-  constexpr int LW = kFewRows / (8 * kWaves), LX = kFewTok / (8 * kWaves);
+  constexpr int LW = kFewRows / (8 * kWaves), LX = NT / (8 * kWaves);
   uint32_t w_off[LW], x_off[LX];
 #pragma unroll
   for (int q = 0; q < LW; ++q) {
@@ -672,8 +676,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_few_kernel(
     const int m = 8 * (kWaves * q + wave) + lane / 8;
     x_off[q] = uint32_t(m) * row_stride + uint32_t(G::swz(m, lane % 8) * 16);
   }
-  const buf_rsrc_t rx = make_rsrc(reinterpret_cast<const char*>(X) + size_t(tb) * kFewTok * row_stride,
-                                  uint32_t(min(kFewTok, n_tok - tb * kFewTok)) * row_stride);
+  const buf_rsrc_t rx = make_rsrc(reinterpret_cast<const char*>(X) + size_t(tb) * NT * row_stride,
+                                  uint32_t(min(NT, n_tok - tb * NT)) * row_stride);
   int pf_g = 0, pf_ks = 0, pf_slot = 0;
   auto issue_stage = [&]() {  // past the last group: empty resources, no access
     const bool live = pf_g < n_groups;
@@ -682,10 +686,11 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_few_kernel(
     const buf_rsrc_t rw =
         make_rsrc(reinterpret_cast<const char*>(W) + size_t(row0) * row_stride, live ? uint32_t(rows) * row_stride : 0u);
     const buf_rsrc_t rxx = live ? rx : make_rsrc(X, 0u);
-    char* dst = lds + pf_slot * kFewStage + 1024 * wave;
+    char* dst = lds + pf_slot * kStage + 1024 * wave;
     const uint32_t soff = uint32_t(pf_ks) * 128u;
 #pragma unroll
-    for (int q = 0; q < LW; ++q) lds_dma16_buf(rw, w_off[q], soff, dst + 1024 * kWaves * q);
+    for (int q = 0; q < LW; ++q)
+      lds_dma16_buf<kStreamW ? kNonTemporal : 0>(rw, w_off[q], soff, dst + 1024 * kWaves * q);
 #pragma unroll
     for (int q = 0; q < LX; ++q) lds_dma16_buf(rxx, x_off[q], soff, dst + kFewRows * 128 + 1024 * kWaves * q);
     pf_slot = pf_slot + 1 == kFewRing ? 0 : pf_slot + 1;
@@ -701,83 +706,118 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_few_kernel(
     b_off[kk] = (kFewRows + fr) * 128 + G::swz(fr, kk * 4 + fq) * 16;
   }
 
-  Ent2 st{-INFINITY, 0.f, 0.f};  // wave 0, lane = token
+  Ent2 st{-INFINITY, 0.f, 0.f};  // waves 0 .. NT / 64 - 1, lane = token
   float zmax = -INFINITY;
   int zarg = INT32_MAX;
-  int slot = 0;
-#pragma unroll
-  for (int q = 0; q < kFewRing - 1; ++q) issue_stage();
-  for (int g = 0; g < n_groups; ++g) {
-    f32x4_t acc[4][4];
+  struct Frags {
+    bf16x8_t a[4], b[NB];
+  };
+  constexpr int kFrags = 4 + NB;
+  auto read_frag = [&](Frags& f, int slot, int kk, int q) {
+    const char* base = lds + slot * kStage;
+    if (q < 4)
+      f.a[q] = *reinterpret_cast<const bf16x8_t*>(base + a_off[kk] + q * 2048);
+    else
+      f.b[q - 4] = *reinterpret_cast<const bf16x8_t*>(base + b_off[kk] + (q - 4) * 2048);
+  };
+  // One k step: its products, with the next step's fragment reads behind every second of them (all reads
+  // ahead of the products, a stage took 2200 cycles for 1024 of matrix-core work).
+  f32x4_t acc[4][NB];
+  auto k_step = [&](const Frags& cur, Frags& nxt, int nslot, int nkk) {
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
-      for (int b = 0; b < 4; ++b) acc[a][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    for (int ks = 0; ks < nk; ++ks) {
-      wait_vm<(kFewRing - 2) * (LW + LX)>();
-      lds_barrier();  // the stage is visible, and nobody reads the one before it any more
-      issue_stage();
-      const char* base = lds + slot * kFewStage;
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        bf16x8_t fa[4], fb[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          fa[q] = *reinterpret_cast<const bf16x8_t*>(base + a_off[kk] + q * 2048);
-          fb[q] = *reinterpret_cast<const bf16x8_t*>(base + b_off[kk] + q * 2048);
-        }
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int b = 0; b < 4; ++b) acc[a][b] = mfma16(fa[a], fb[b], acc[a][b]);
+      for (int b = 0; b < NB; ++b) {
+        const int m = a * NB + b;
+        acc[a][b] = mfma16(cur.a[a], cur.b[b], acc[a][b]);
+        if (m % 2 == 0 && m / 2 < kFrags) read_frag(nxt, nslot, nkk, m / 2);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      slot = slot + 1 == kFewRing ? 0 : slot + 1;
+  };
+  static_assert(2 * (kFrags - 1) < 4 * NB, "fragment reads fit behind the products");
+  int slot = 0;
+#pragma unroll
+  for (int q = 0; q < kFewRing; ++q) issue_stage();
+  wait_vm<(kFewRing - 1) * (LW + LX)>();
+  lds_barrier();
+  Frags f0, f1;
+#pragma unroll
+  for (int q = 0; q < kFrags; ++q) read_frag(f0, 0, 0, q);
+  for (int g = 0; g < n_groups; ++g) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) acc[a][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int ks = 0; ks < nk; ++ks) {
+      const int next = slot + 1 == kFewRing ? 0 : slot + 1;
+      k_step(f0, f1, slot, 1);
+      // the next stage has landed, and this wave's reads of the stage are done: after the barrier nobody
+      // reads its slot again
+      wait_vm<(kFewRing - 2) * (LW + LX)>();
+      lds_barrier();
+      issue_stage();
+      k_step(f1, f0, next, 0);
+      slot = next;
     }
     // acc[a][b][r]: tile 2 wave + a / 2 of the group, 16-row block i = 4 (a % 2) + fq, row r; token 16 b + fr
+    auto store = [&](auto half_c, int q) {  // the wave's tile half_c into place q
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            logits[(q * 32 + 4 * (4 * a + fq) + r) * kPitch + 16 * b + fr] = acc[2 * decltype(half_c)::value + a][b][r];
+    };
+    for (int c = 0; c < kFewTiles / CT; ++c) {
       lds_barrier();  // the logits before these are folded
-      if ((wave >> 1) == c) {
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int b = 0; b < 4; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              logits[((2 * (wave & 1) + a / 2) * 32 + 4 * (4 * (a % 2) + fq) + r) * kFewPitch + 16 * b + fr] =
-                  acc[a][b][r];
+      for (int q = 0; q < CT; ++q) {
+        const int tile = c * CT + q;
+        if (wave == tile / 2) {
+          if (tile % 2 == 0)
+            store(std::integral_constant<int, 0>{}, q);
+          else
+            store(std::integral_constant<int, 1>{}, q);
+        }
       }
       lds_barrier();
-      if (wave == 0) {
-        for (int q = 0; q < 4; ++q) {
-          const int tile = kFewTiles * g + 4 * c + q;
+      if (wave < NT / 64) {
+        for (int q = 0; q < CT; ++q) {
+          const int tile = kFewTiles * g + c * CT + q;
           if (tile >= n_my) break;
           float z[kNB][4];
 #pragma unroll
           for (int i = 0; i < kNB; ++i)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) z[i][r] = logits[(q * 32 + 4 * i + r) * kFewPitch + lane];
+            for (int r = 0; r < 4; ++r) z[i][r] = logits[(q * 32 + 4 * i + r) * kPitch + 64 * wave + lane];
           const int vt = vs + tile * n_vsplit;
           const bool ragged = (vt + 1) * kBV > V;
           const int row0 = vt * kBV + wv * 128 + 4 * sq, lim = V - row0;
           st = fold_tile(st, tile == 0, ragged, lim, [&](int i, int r) { return z[i][r]; });
           if (kArg) {
+            float tb = -INFINITY;  // the tile's largest live logit
 #pragma unroll
             for (int i = 0; i < kNB; ++i)
 #pragma unroll
-              for (int r = 0; r < 4; ++r) {  // rows ascend: strict keeps the lowest among equal logits
-                const bool up = (!ragged | (i * 16 + r < lim)) & (z[i][r] > zmax);
-                zmax = up ? z[i][r] : zmax;
-                zarg = up ? row0 + i * 16 + r : zarg;
-              }
+              for (int r = 0; r < 4; ++r) tb = fmaxf(tb, !ragged || i * 16 + r < lim ? z[i][r] : -INFINITY);
+            const bool up = tb > zmax;  // strict: an earlier tile keeps equal maxima
+            if (__any(up)) {  // seldom past the first tiles: the lowest row holding it
+              int k = 0;
+#pragma unroll
+              for (int i = kNB - 1; i >= 0; --i)
+#pragma unroll
+                for (int r = 3; r >= 0; --r) k = z[i][r] == tb ? 16 * i + r : k;
+              zmax = up ? tb : zmax;
+              zarg = up ? row0 + k : zarg;
+            }
           }
         }
       }
     }
   }
   wait_vm<0>();  // no transfer into LDS outlives the workgroup
-  const int tok = tb * kFewTok + lane;
-  if (wave == 0 && tok < n_tok) {
+  const int tok = tb * NT + 64 * wave + lane;
+  if (wave < NT / 64 && tok < n_tok) {
     const size_t o = size_t(state) * n_tok + tok;
     part_m[o] = st.m;
     part_s[o] = st.s;
@@ -835,18 +875,23 @@ __global__ __launch_bounds__(256) void entropy_few_merge_kernel(const float* __r
   if (arg) arg[tok] = ib;
 }
 
-// Whether a call takes entropy_few_kernel: an estimate of both kernels in thousands of cycles, rounds of
-// workgroups over the chip times a workgroup's stages and folds.
+// Tokens per workgroup of entropy_few_kernel: 64 also for two blocks of them, which fill the chip (128 tokens
+// 266 us with 64, 315 with 128 a workgroup; 256 tokens 435 and 316).
+inline int few_tokens(int64_t n_tok) { return n_tok <= 128 ? 64 : 128; }
+
+// Whether a call takes entropy_few_kernel: an estimate of both kernels in us, rounds of workgroups over the
+// chip times a workgroup's stages and folds (fitted to MI355X at d 2048 and 4096), with a margin: near it the
+// two are within 10% of each other.
 inline bool use_few(int64_t n_tok, int d, int n_vt) {
-  const int slices = choose_vsplit(n_vt);
+  const int slices = choose_vsplit(n_vt), nt = few_tokens(n_tok);
   if (n_tok > kFewMaxTok || d % 64 != 0) return false;
   if (size_t((kFewTiles - 1) * slices + 1) * kBV * size_t(d) * 2 >= (size_t(1) << 32)) return false;  // 32-bit offsets
   const int nk = d / 64, tiles = (n_vt + slices - 1) / slices, groups = (tiles + kFewTiles - 1) / kFewTiles;
-  const int few_wgs = 8 * slices * int((n_tok + kFewTok - 1) / kFewTok);
+  const int few_wgs = 8 * slices * int((n_tok + nt - 1) / nt);
   const int gemm_wgs = slices * int((n_tok + kBT - 1) / kBT);
-  const float few = float((few_wgs + 255) / 256) * float(groups) * (0.9f * float(nk) + 8.5f);
-  const float gemm = float((gemm_wgs + 255) / 256) * float(tiles) * (2.05f * float(nk) + 8.f);
-  return few < 0.9f * gemm;
+  const float few = float((few_wgs + 255) / 256) * float(groups) * (0.94f * float(nk) + 4.f);
+  const float gemm = float((gemm_wgs + 255) / 256) * float(tiles) * (float(nk) + 5.6f);
+  return few < 0.85f * gemm;
 }
 
 // Merge the partial states of each token and write H in nats: H = ln2 * (log2 s - t / s).  With
@@ -989,13 +1034,16 @@ int launch_token_entropy(const void* X, const void* W, int n, int d, int V, int 
     ESTP_CHECK_LAUNCH("entropy_f32_kernel");
     merge(0, n, n_vsplit, 0);
   } else if (use_few(n, d, n_vt)) {
-    const int n_vsplit = choose_vsplit(n_vt), n_tb = (n + kFewTok - 1) / kFewTok;
+    const int n_vsplit = choose_vsplit(n_vt), nt = few_tokens(n), n_tb = (n + nt - 1) / nt;
     const dim3 grid(unsigned(8 * n_vsplit * n_tb)), block(kWaves * 64);
     auto go = [&](auto kernel) {
       kernel<<<grid, block, 0, s>>>(static_cast<const uint16_t*>(X), static_cast<const uint16_t*>(W), n, d, V, n_vsplit,
                                     n_vt, n_tb, pm, ps, pt, pz, pa);
     };
-    want_arg ? go(entropy_few_kernel<true>) : go(entropy_few_kernel<false>);
+    if (nt == 64)
+      want_arg ? go(entropy_few_kernel<64, true, true>) : go(entropy_few_kernel<64, false, true>);
+    else
+      want_arg ? go(entropy_few_kernel<128, true, false>) : go(entropy_few_kernel<128, false, false>);
     ESTP_CHECK_LAUNCH("entropy_few_kernel");
     entropy_few_merge_kernel<<<dim3((n + 15) / 16), dim3(256), 0, s>>>(pm, ps, pt, pz, pa, n, n_vsplit, H,
                                                                        vocab_argmax);

@@ -43,10 +43,12 @@ __device__ __forceinline__ buf_rsrc_t make_rsrc(const void* base, uint32_t bytes
 // 16-byte buffer -> LDS transfer (buffer_load_dwordx4 ... lds): lane l reads
 // the 16 bytes at voffset(l) + soffset of the resource; they land in LDS at
 // dst_wave_base + 16 * l.  `soffset` and `dst_wave_base` must be uniform.
+constexpr int kNonTemporal = 2;  // cache-policy bit of a transfer: a line used once
+template <int kPolicy = 0>
 __device__ __forceinline__ void lds_dma16_buf(buf_rsrc_t r, uint32_t voffset, uint32_t soffset,
                                               void* dst_wave_base) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, to_lds(dst_wave_base), 16, voffset, soffset, 0, 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, to_lds(dst_wave_base), 16, voffset, soffset, 0, kPolicy);
 #endif
 }
 
