@@ -120,6 +120,10 @@ __device__ __forceinline__ void arg_merge(float& av, int& ai, float bv, int bi) 
 // logits exceed the reference by more than 2^64 in weight (or overflow) is
 // refolded exactly with its own max.  The ragged last vocabulary tile always
 // takes the exact, masked path.
+//
+// entropy_gemm_kernel holds the same steps written out: through this function its
+// next-token mode kernel spilled 17 instead of 13 registers and took 1% longer
+// (8192 tokens, V 151936, d 1536).  test_few_tokens_change_no_bit holds the two equal.
 template <typename Z>
 __device__ __forceinline__ Ent2 fold_tile(Ent2 e, bool first, bool ragged, int lim, Z&& z) {
   bool exact = ragged;
@@ -192,8 +196,15 @@ __device__ __forceinline__ Ent2 fold_tile(Ent2 e, bool first, bool ragged, int l
 struct SlicePlan {
   int main_tiles;
   int tail_slices;
-  int tail_cols;  // token tiles of one slice that run next to each other on one XCD (0: plain order)
+  int tail_cols;  // token tiles of one slice that run next to each other on one XCD (0: no tail of its own)
 };
+
+// Index of token tok's partial state from the vs-th of its slices (a plan with a tail of its own).
+__device__ __forceinline__ size_t tail_state(const SlicePlan& p, int n_tok, int vs, int tok) {
+  const int main_tok = p.main_tiles * kBT;
+  return tok < main_tok ? size_t(vs) * main_tok + tok
+                        : size_t(kMaxVsplit) * main_tok + size_t(vs) * (n_tok - main_tok) + (tok - main_tok);
+}
 
 // Partial states per array that a call's workspace holds: one per token and slice (at most kMaxVsplit), or
 // entropy_few_kernel's 8 per token and slice, or, while the no-allocation entry point's fixed scratch has room
@@ -252,11 +263,15 @@ inline size_t plan_workgroups(const SlicePlan& p, int64_t n_tok) {
 // after it the two freed slots take parts 2s + P and 2s + P + 1.  With P odd
 // the W part of a stage is issued one stage before its X part, and about
 // (P - 2) / 2 stages of loads are in flight while a stage is consumed.
-template <int P, int BK, bool kArg>
+//
+// kTail: the tiles past the last whole group are cut as the plan says (tail_cols > 0).  Otherwise every tile
+// takes n_slices slices and the partial states are [n_slices, n_tok].  With one kernel for both, calls without
+// such a tail took 0.26% longer (65536 tokens, V 128256, d 4096: 47.58 ms, 47.46 with two).
+template <int P, int BK, bool kArg, bool kTail>
 __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
-    const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int n_tok, int d, int V, SlicePlan pl,
+    const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int n_tok, int d, int V, int n_slices,
     int n_vt, int n_tt, float* __restrict__ part_m, float* __restrict__ part_s, float* __restrict__ part_t,
-    float* __restrict__ part_zmax, int* __restrict__ part_arg) {
+    float* __restrict__ part_zmax, int* __restrict__ part_arg, SlicePlan pl) {
   using G = Geom<BK>;
   constexpr int L = G::L;
   constexpr int kSub = G::kSub;
@@ -273,44 +288,40 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
   const int wt = wave >> 1;  // which 128-token half of the token tile
 
   // ---- workgroup -> (vocabulary slice, token tile)
-  int vs, tt, n_vsplit;
-  size_t part_off;   // this workgroup's row of the partial states, less its first token
+  int vs, tt;
+  int n_vsplit = n_slices;
   {
     const int bid = blockIdx.x;
     constexpr int R = 32;  // workgroups resident on one XCD
-    const int n_main = pl.main_tiles * kMaxVsplit;
-    if (bid < n_main) {
-      // whole dispatch waves of 16 token tiles x 16 slices
+    // whole dispatch waves of 16 token tiles x 16 slices take the XCD-aware order
+    const int n_full = kTail               ? pl.main_tiles * kMaxVsplit
+                       : n_vsplit == 16 ? (n_tt / (R / 2)) * (R / 2) * 16
+                                        : 0;
+    if (bid < n_full) {
       const int xcd = bid & 7, j = bid >> 3;
       const int wave_idx = j / R, jj = j % R;
-      n_vsplit = kMaxVsplit;
+      if (kTail) n_vsplit = kMaxVsplit;
       vs = (jj & 3) * 4 + (xcd & 3);
       tt = wave_idx * (R / 2) + (xcd >> 2) * (R / 4) + (jj >> 2);
-      part_off = size_t(vs) * min(n_tok, pl.main_tiles * kBT);
+    } else if (!kTail) {  // the token tiles past the last whole group follow in plain order
+      const int r = bid - n_full;
+      vs = r % n_vsplit;
+      tt = n_full / n_vsplit + r / n_vsplit;
     } else {
-      // the tiles past them
-      int r = bid - n_main, in_tail;
+      // an eighth of the workgroups to each XCD (n_full is a multiple of 8), in an order that
+      // puts the tail_cols token tiles of one slice next to each other: they stream the same
+      // rows of W through one L2.  The second group of columns holds what is left of the tiles.
       n_vsplit = pl.tail_slices;
-      if (pl.tail_cols == 0) {  // plain order, slice fastest
-        vs = r % n_vsplit;
-        in_tail = r / n_vsplit;
-      } else {
-        // an eighth of the workgroups to each XCD (n_main is a multiple of 8), in an order that
-        // puts the tail_cols token tiles of one slice next to each other: they stream the same
-        // rows of W through one L2.  The second group of columns holds what is left of the tiles.
-        const int n_wg = (n_tt - pl.main_tiles) * n_vsplit, per_xcd = (n_wg + 7) / 8;
-        r = (r & 7) * per_xcd + (r >> 3);
-        if (r >= n_wg) return;  // the grid is rounded up
-        const int n_first = pl.tail_cols * n_vsplit;
-        const bool second = r >= n_first;
-        const int cols = second ? n_tt - pl.main_tiles - pl.tail_cols : pl.tail_cols;
-        if (second) r -= n_first;
-        vs = r / cols;
-        in_tail = (second ? pl.tail_cols : 0) + r % cols;
-      }
-      tt = pl.main_tiles + in_tail;
-      const int first = pl.main_tiles * kBT;
-      part_off = size_t(kMaxVsplit) * first + size_t(vs) * (n_tok - first) - first;
+      int r = bid - n_full;
+      const int n_wg = (n_tt - pl.main_tiles) * n_vsplit, per_xcd = (n_wg + 7) / 8;
+      r = (r & 7) * per_xcd + (r >> 3);
+      if (r >= n_wg) return;  // the grid is rounded up
+      const int n_first = pl.tail_cols * n_vsplit;
+      const bool second = r >= n_first;
+      const int cols = second ? n_tt - pl.main_tiles - pl.tail_cols : pl.tail_cols;
+      if (second) r -= n_first;
+      vs = r / cols;
+      tt = pl.main_tiles + (second ? pl.tail_cols : 0) + r % cols;
     }
   }
   const int nk = d / BK;
@@ -498,13 +509,76 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
 
     // ---- fold the finished tile into the running states.  acc[i][j][r] is the
     // logit of vocabulary row vt*256 + wv*128 + 16 i + 4 fq + r for token
-    // tt*256 + wt*128 + 16 j + fr.
+    // tt*256 + wt*128 + 16 j + fr.  The steps are fold_tile's.
     const int vt = vs + tile * n_vsplit;
     const bool ragged = (vt + 1) * kBV > V;
     const int lim = V - (vt * kBV + wv * 128 + 4 * fq);  // live rows: 16 i + r < lim
 #pragma unroll
-    for (int j = 0; j < kNB; ++j)
-      st[j] = fold_tile(st[j], tile == 0, ragged, lim, [&](int i, int r) { return acc[i][j][r]; });
+    for (int j = 0; j < kNB; ++j) {
+      Ent2 e = st[j];
+      bool exact = ragged;
+      if (!ragged) {
+        if (tile == 0) {  // first tile: the tile's own max is the reference
+          float mx = acc[0][j][0];
+#pragma unroll
+          for (int i = 0; i < kNB; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, acc[i][j][r]);
+          e = Ent2{mx * kLog2e, 0.f, 0.f};
+        }
+        float s = e.s, t = e.t;
+#pragma unroll
+        for (int i = 0; i < kNB; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float dd = fmaf(acc[i][j][r], kLog2e, -e.m);
+            const float p = fast_exp2(dd);
+            s += p;
+            t = fmaf(p, dd, t);
+          }
+        if (s <= 0x1p64f) {
+          e.s = s;
+          e.t = t;
+        } else {
+          exact = true;  // overflow (or a logit far above the reference): refold exactly
+        }
+      }
+      if (exact) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < kNB; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const bool live = !ragged || i * 16 + r < lim;
+            mx = live ? fmaxf(mx, acc[i][j][r]) : mx;
+          }
+        const float mnew = fmaxf(e.m, mx * kLog2e);
+        const float dl = fmaxf(e.m - mnew, kExp2Floor);
+        const float sc = fast_exp2(dl);
+        float s = sc * e.s;
+        float t = sc * (e.t + e.s * dl);
+#pragma unroll
+        for (int i = 0; i < kNB; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            // dead rows enter as -inf: dd clamps to the floor and adds 0 * floor,
+            // also while mnew is still -inf (a lane with no live row yet)
+            const bool live = !ragged || i * 16 + r < lim;
+            const float dd = fmaxf(fmaf(live ? acc[i][j][r] : -INFINITY, kLog2e, -mnew), kExp2Floor);
+            const float p = fast_exp2(dd);
+            s += p;
+            t = fmaf(p, dd, t);
+          }
+        e = Ent2{mnew, s, t};
+      }
+      // rebase to the running log-sum-exp: m += log2 s, s = 1, t = t / s - log2 s
+      // (s >= 1 here: the reference never exceeds the largest logit seen, in base 2)
+      if (e.s > 0.f) {
+        const float dl = fast_log2(e.s);
+        e = Ent2{e.m + dl, 1.f, e.t / e.s - dl};
+      }
+      st[j] = e;
+    }
     if (kArg) {
       // the next-token mode, in a loop of its own so that the eight columns' independent compare
       // chains interleave.  Per column: the tile's largest live logit, then the lowest of the
@@ -594,7 +668,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
       Ent2 r = ent2_merge(st[j], Ent2{p[0], p[1], p[2]});
       const int tok = tt * kBT + tl;
       if (tok < n_tok) {
-        const size_t o = part_off + tok;
+        const size_t o = kTail ? tail_state(pl, n_tok, vs, tok) : size_t(vs) * n_tok + tok;
         part_m[o] = r.m;
         part_s[o] = r.s;
         part_t[o] = r.t;
@@ -611,7 +685,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
         float zb = zmax[c];
         int ib = zarg[c];
         arg_merge(zb, ib, p[3], __float_as_int(p[4]));
-        const size_t o = part_off + tok;
+        const size_t o = kTail ? tail_state(pl, n_tok, vs, tok) : size_t(vs) * n_tok + tok;
         part_zmax[o] = zb;
         part_arg[o] = ib;
       }
@@ -1050,24 +1124,25 @@ int launch_token_entropy(const void* X, const void* W, int n, int d, int V, int 
   } else {
     const SlicePlan pl = plan_slices(n, n_vt);
     const dim3 grid(unsigned(plan_workgroups(pl, n))), block(kWaves * 64);
-    const uint16_t* Xh = static_cast<const uint16_t*>(X);
-    const uint16_t* Wh = static_cast<const uint16_t*>(W);
-    if (d % 64 == 0) {
-      if (want_arg)
-        entropy_gemm_kernel<5, 64, true><<<grid, block, 0, s>>>(Xh, Wh, n, d, V, pl, n_vt, n_tt, pm, ps, pt, pz, pa);
+    auto go = [&](auto kernel) {
+      kernel<<<grid, block, 0, s>>>(static_cast<const uint16_t*>(X), static_cast<const uint16_t*>(W), n, d, V,
+                                    pl.tail_slices, n_vt, n_tt, pm, ps, pt, want_arg ? pz : nullptr,
+                                    want_arg ? pa : nullptr, pl);
+    };
+    if (pl.tail_cols > 0) {
+      if (d % 64 == 0)
+        want_arg ? go(entropy_gemm_kernel<5, 64, true, true>) : go(entropy_gemm_kernel<5, 64, false, true>);
       else
-        entropy_gemm_kernel<5, 64, false><<<grid, block, 0, s>>>(Xh, Wh, n, d, V, pl, n_vt, n_tt, pm, ps, pt, nullptr,
-                                                                 nullptr);
+        want_arg ? go(entropy_gemm_kernel<9, 32, true, true>) : go(entropy_gemm_kernel<9, 32, false, true>);
     } else {
-      if (want_arg)
-        entropy_gemm_kernel<9, 32, true><<<grid, block, 0, s>>>(Xh, Wh, n, d, V, pl, n_vt, n_tt, pm, ps, pt, pz, pa);
+      if (d % 64 == 0)
+        want_arg ? go(entropy_gemm_kernel<5, 64, true, false>) : go(entropy_gemm_kernel<5, 64, false, false>);
       else
-        entropy_gemm_kernel<9, 32, false><<<grid, block, 0, s>>>(Xh, Wh, n, d, V, pl, n_vt, n_tt, pm, ps, pt, nullptr,
-                                                                 nullptr);
+        want_arg ? go(entropy_gemm_kernel<9, 32, true, false>) : go(entropy_gemm_kernel<9, 32, false, false>);
     }
     ESTP_CHECK_LAUNCH("entropy_gemm_kernel");
-    const int n_main = std::min(n, pl.main_tiles * kBT);
-    merge(0, n_main, kMaxVsplit, 0);
+    const int n_main = pl.tail_cols > 0 ? pl.main_tiles * kBT : n;
+    merge(0, n_main, pl.tail_cols > 0 ? kMaxVsplit : pl.tail_slices, 0);
     merge(n_main, n - n_main, pl.tail_slices, size_t(kMaxVsplit) * n_main);
   }
   ESTP_CHECK_LAUNCH("entropy_merge_kernel");
