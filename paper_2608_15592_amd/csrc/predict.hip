@@ -21,6 +21,8 @@ namespace estp {
 namespace detail {
 
 constexpr int kKChunk = 256;  // the depth of the first layer is never split finer over workgroups than this
+constexpr int kMaxDepth = 65536 * kKChunk;
+static_assert(size_t(kMaxDepth) * 32 * 4 < kPastEnd, "byte offsets within the narrow tile's rows");
 
 __device__ __forceinline__ float act_fn(float x, int act) {
   if (act == ESTP_ACT_RELU) return fmaxf(x, 0.f);
@@ -155,9 +157,10 @@ int launch_mlp_tiles(const float* P, const float* W1, int B, int d, int Hd, floa
 }
 // Tiles of 64 x 64, which read half as much per product, where there are at least 64 of them; else of 32 x 32,
 // which spread over more CUs (us per estp_predict call on MI355X with 32 and with 64: 4096 -> 1024, 2048
-// prompts 281 and 173, 256 prompts 42 and 33, one prompt 12 and 16; 1536 -> 256, 256 prompts 17 and 20).
+// prompts 281 and 173, 256 prompts 42 and 33, one prompt 12 and 16; 1536 -> 256, 256 prompts 17 and 20).  A
+// tile's rows have to end below kPastEnd, in bytes: the deepest inputs take the narrow tile.
 int launch_mlp_partial(const float* P, const float* W1, int B, int d, int Hd, float* part, hipStream_t s) {
-  const bool wide = ((size_t(B) + 63) / 64) * ((size_t(Hd) + 63) / 64) >= 64;
+  const bool wide = ((size_t(B) + 63) / 64) * ((size_t(Hd) + 63) / 64) >= 64 && size_t(d) * 256 <= kPastEnd;
   return wide ? launch_mlp_tiles<4, 8>(P, W1, B, d, Hd, part, s) : launch_mlp_tiles<2, 16>(P, W1, B, d, Hd, part, s);
 }
 
@@ -552,6 +555,7 @@ extern "C" int estp_predict(const float* pooled, int32_t B, int32_t d, const flo
                "estp_predict: pooled, W1, W2 and yhat must be non-null");
   ESTP_REQUIRE(B >= 1 && B <= 65536 && d >= 1 && hidden >= 1 && K >= 1 && K <= 1024, ESTP_ERR_INVALID_ARG,
                "estp_predict: need 1 <= B <= 65536, d >= 1, hidden >= 1, 1 <= K <= 1024");
+  ESTP_REQUIRE(d <= kMaxDepth, ESTP_ERR_UNSUPPORTED, "estp_predict: d %d exceeds %d", d, kMaxDepth);
   ESTP_REQUIRE(K == 1 || centres, ESTP_ERR_INVALID_ARG, "estp_predict: centres required when K > 1");
   ESTP_REQUIRE(act == ESTP_ACT_RELU || act == ESTP_ACT_GELU_TANH, ESTP_ERR_INVALID_ARG,
                "estp_predict: unknown activation %d", act);
@@ -605,6 +609,7 @@ extern "C" int estp_head_train_step(const float* pooled, const float* y, int32_t
                "estp_head_train_step: need 1 <= B <= 65536, hidden >= 1, 2 <= K <= 1024");
   ESTP_REQUIRE(d >= 4 && d % 4 == 0, ESTP_ERR_INVALID_ARG,
                "estp_head_train_step: d must be a positive multiple of 4, got %d", d);
+  ESTP_REQUIRE(d <= kMaxDepth, ESTP_ERR_UNSUPPORTED, "estp_head_train_step: d %d exceeds %d", d, kMaxDepth);
   ESTP_REQUIRE(act == ESTP_ACT_RELU || act == ESTP_ACT_GELU_TANH, ESTP_ERR_INVALID_ARG,
                "estp_head_train_step: unknown activation %d", act);
   ESTP_REQUIRE(step >= 1, ESTP_ERR_INVALID_ARG, "estp_head_train_step: step counts from 1, got %d", step);

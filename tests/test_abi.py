@@ -196,6 +196,16 @@ def test_predict_validation():
     assert call(wsb=ws - 1) == 3
 
 
+@needs_no_gpu
+@pytest.mark.parametrize("d,code", [(65536 * 256, 3), (65536 * 256 + 4, 2)])
+def test_head_depth_limit(d, code):
+    """The deepest input passes the size check (refused for its workspace here), one past it does not."""
+    lib = estp.load()
+    assert lib.estp_predict(FAKE, 1, d, FAKE, None, 1, 0, FAKE, None, 1, FAKE, FAKE, None, None, WS, 0, None) == code
+    assert lib.estp_head_train_step(FAKE, FAKE, 1, d, 1, 2, 0, FAKE, FAKE, FAKE, FAKE, FAKE, 1, 0.5, 1e-3, 0.9, 0.999,
+                                    1e-8, 0.0, None, WS, 0, None) == code
+
+
 def test_binding_fails_loudly_without_library(tmp_path):
     with pytest.raises(RuntimeError):
         _lib.load.__wrapped__(str(tmp_path / "missing.so")) if hasattr(_lib.load, "__wrapped__") else \
