@@ -162,9 +162,11 @@ ESTP_API int estp_token_entropy_noalloc(const void* X, const void* W, int64_t n_
  * queries of the causal attention it receives, averaged over the query heads,
  * summed over the L layers given.  The diagonal A_jj is included.  Query head
  * h reads key head g(h) = h / (Hq / Hkv).  The N x N attention never reaches
- * memory: pass 1 records each query row's log-sum-exp, pass 2 re-forms the
- * scores per key block and sums exp(s - lse) over the later queries.  Each
- * prompt's S sums to L.
+ * memory.  Short prompts (at most 2048 tokens, by a rule on the call's shape)
+ * take one pass that keeps the exponentials of whole rows in registers until
+ * their sums are known; otherwise pass 1 records each query row's log-sum-exp
+ * and pass 2 re-forms the scores per key block and sums exp(s - lse) over the
+ * later queries.  Each prompt's S sums to L.
  *
  *   Q  [L, n_tok, Hq, dh]   post-RoPE queries (dtype), 16-byte aligned
  *   K  [L, n_tok, Hkv, dh]  post-RoPE keys (dtype), 16-byte aligned
@@ -215,9 +217,9 @@ ESTP_API int estp_attn_importance_from_lse(const void* Q, const void* K, const f
  * are still the causal softmax over j <= i).  This is the other reading of
  * the paper's note on self-similarity.
  *
- *   lse            NULL: the row log-sum-exps are computed (two passes, as
+ *   lse            NULL: the row log-sum-exps are computed (as
  *                  estp_attn_importance); else the caller's natural-log
- *                  [L, Hq, n_tok] row normalisers (one pass, as
+ *                  [L, Hq, n_tok] row normalisers (as
  *                  estp_attn_importance_from_lse)
  *   layer_weights  host float32 [L], finite, at most 64 layers; NULL = all 1
  *   flags          0 or ESTP_IMPORTANCE_EXCLUDE_SELF
@@ -270,7 +272,8 @@ ESTP_API int estp_combine_pool(const void* X, const float* S, const float* H, co
  *   yhat [B]            float32 output
  *   bin  [B]            int32 output or NULL (written only when K > 1)
  *   order [B]           int32 output or NULL
- * Requires B >= 1, d >= 1, hidden >= 1, 1 <= K <= 1024, B <= 65536.
+ * Requires B >= 1, d >= 1, hidden >= 1, 1 <= K <= 1024, B <= 65536; d > 16777216
+ * returns ESTP_ERR_UNSUPPORTED.
  * ------------------------------------------------------------------------ */
 ESTP_API size_t estp_predict_workspace_size(int32_t B, int32_t d, int32_t hidden, int32_t K);
 ESTP_API int estp_predict(const float* pooled, int32_t B, int32_t d, const float* W1, const float* b1, int32_t hidden,
