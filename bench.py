@@ -2,7 +2,7 @@
 """Throughput of the ESTP scoring and pooling path on one MI355X.
 
 One step = the whole path over one batch: token entropy (fused LM-head GEMM),
-attention importance (two passes), fusion + pooling, length head + SJF order,
+attention importance, fusion + pooling, length head + SJF order,
 enqueued back to back on one stream, inputs resident in HBM.  Prints one JSON
 line with prompt tokens/s, the roofline position of the dominant kernel
 (entropy GEMM, bf16 matrix cores) and the fp64 oracle timed on the host as a
@@ -393,7 +393,7 @@ def main() -> int:
     torch.cuda.synchronize()
     lse_ms = float(np.mean([lse_evs[k].elapsed_time(lse_evs[k + 1]) for k in range(5)]))
     del lse, ws_lse, S_lse
-    log(f"importance from prefill LSE: {lse_ms:.3f} ms (two-pass call {imp_ms:.3f} ms)")
+    log(f"importance from prefill LSE: {lse_ms:.3f} ms (full call {imp_ms:.3f} ms)")
 
     # One training step of a 16-bin head on the step's pooled vectors (Eq. 6-8, AdamW), timed on
     # its own: W1 [1024, d] dominates, read and written with its two moments.
@@ -486,7 +486,7 @@ def main() -> int:
 
     ent_flop = 2.0 * n_tok * w.V * w.d
     imp_flop_alg = float(sum(int(T) * int(T) for T in inp["lengths"])) * w.dh * w.Hq * w.L  # one causal QK^T
-    imp_exps = 2.0 * float(sum(int(T) * (int(T) + 1) // 2 for T in inp["lengths"])) * w.Hq * w.L  # two passes
+    imp_exps = float(sum(int(T) * (int(T) + 1) // 2 for T in inp["lengths"])) * w.Hq * w.L  # one per causal score
     pool_bytes = n_tok * w.d * 2 + n_tok * 4 + B * w.d * 4
     ent_tflops = ent_flop / (ent_ms * 1e-3) / 1e12
     pool_gbps = pool_bytes / (pool_ms * 1e-3) / 1e9
@@ -535,8 +535,8 @@ def main() -> int:
         "kernels_ms_median": dict(zip(("token_entropy", "attn_importance", "combine_pool", "predict"),
                                       (float(v) for v in med_ms))),
         "importance": {"alg_flop": imp_flop_alg, "alg_tflops": imp_flop_alg / (imp_ms * 1e-3) / 1e12,
-                       "executed_tflops": 2 * imp_flop_alg / (imp_ms * 1e-3) / 1e12,
-                       # each causal score is exponentiated once per pass; v_exp_f32 issues at a quarter of
+                       # every causal score counted once (calls that take two passes exponentiate it twice);
+                       # v_exp_f32 issues at a quarter of
                        # the FMA rate: 256 CUs x 4 SIMDs x 16 lanes / 4 x 2.4 GHz
                        "exp_roofline": {"bound": "alu", "exps": imp_exps, "achieved": imp_exps / (imp_ms * 1e-3),
                                         "peak": PEAK_EXP_PER_S, "unit": "exp/s",
@@ -544,7 +544,7 @@ def main() -> int:
         "entropy_with_vocab_argmax": {"ms": am_ms, "plain_ms": plain_ms, "overhead": am_ms / plain_ms - 1.0,
                                       "note": "estp_token_entropy with the vocab_argmax output against the plain "
                                               "call, interleaved, median of 3 each; not part of the timed step"},
-        "importance_from_prefill_lse": {"ms": lse_ms, "vs_two_pass": lse_ms / imp_ms,
+        "importance_from_prefill_lse": {"ms": lse_ms, "vs_full_call": lse_ms / imp_ms,
                                         "note": "estp_attn_importance_from_lse with given row LSEs; not part of "
                                                 "the timed step"},
         "head_train_step": {"ms": tr_ms, "head": f"{w.d}->{Hd_tr}->{K_tr}", "batch": B, "param_bytes_rw": tr_bytes,
