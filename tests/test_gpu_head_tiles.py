@@ -1,6 +1,6 @@
 """Length head and its training step at the edges of their tiles, against the fp64 oracle: 32 prompts x 32
-hidden units and depth ranges of 16 waves in the first layer, 32 x 128 tiles of the gradients, four outputs
-at a time in the second layer."""
+hidden units and depth ranges of 16 waves in the first layer (64 x 64 and 8 waves in larger calls), 32 x 128
+tiles of the gradients, four outputs at a time in the second layer."""
 import numpy as np
 import pytest
 import torch
@@ -28,6 +28,8 @@ def _head(g, d, Hd, K):
     (257, 4096, 40, 3),    # deep and narrow: several depth shares
     (5, 4100, 1000, 1024), # the most outputs
     (1100, 64, 70, 50),    # more than one LDS round of the order
+    (257, 132, 1000, 16),  # 64 x 64 tiles, one prompt past a tile, depth past a step
+    (300, 131, 961, 4),    # the same with single loads, one hidden unit past a tile
 ])
 def test_predict_tiles(B, d, Hd, K):
     g = np.random.default_rng(B + d)
