@@ -233,6 +233,9 @@ __global__ __launch_bounds__(64 * W, 2) void attn_onepass_kernel(const uint16_t*
 #pragma unroll
         for (int k = 0; k < kBlocks; ++k) csum[k] += k == c ? s : 0.f;
       }
+      // Every wave has read this row block's queries: the caller's next transfers go into their buffer, and a
+      // wave with few key blocks (none, in a prompt's first row blocks) would issue them while others still read.
+      __syncthreads();
     };
 
     // ---- one row block against this wave's CNT key blocks; one body per CNT, so that the scores stay in

@@ -94,3 +94,54 @@ def test_onepass_not_a_number_stays_in_its_rows():
     S = host(estp.attn_importance(dev(I.f32_to_bf16_bits(q)), dev(K), dev(cu), 200))
     assert np.all(np.isnan(S[:71]))
     assert np.all(np.isfinite(S[71:]))
+
+
+def _walk(lengths, L, Hq, Hkv):
+    """Row blocks that one workgroup of the one-pass kernel takes at least, over its heads, in the longest prompt: the
+    shares of a call reach four (eight waves) or eight workgroups per compute unit and no further."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    G, nrb = Hq // Hkv, (max(lengths) + 31) // 32
+    want = (4 if max(lengths) > 1024 else 8) * cus
+    units = len(lengths) * L * Hkv
+    rsplit, hsplit = max(1, min(8, G * nrb // 16)), 1
+    while rsplit < min(8, nrb) and units * rsplit < want:
+        rsplit += 1
+    while hsplit < G and (G % hsplit or units * rsplit * hsplit < want):
+        hsplit += 1
+    if units * rsplit * hsplit < want:
+        rsplit = min(nrb, -(-want // (units * hsplit)))
+    return nrb // rsplit * (G // hsplit)
+
+
+# workgroups of four and of eight waves that walk several row blocks of several heads
+WALK_CASES = [([512] * 16, 1, 32, 8, 128), ([1057] * 8, 1, 32, 8, 32), ([330, 500, 441] * 11, 1, 8, 4, 64)]
+
+
+@pytest.mark.parametrize("rows", ["first-low", "first-high", "middle", "scattered", "all"])
+@pytest.mark.parametrize("lengths,L,Hq,Hkv,dh", WALK_CASES, ids=["w4-dh128", "w8-dh32", "w4-dh64-ragged"])
+def test_onepass_sums_out_of_range_between_others(lengths, L, Hq, Hkv, dh, rows):
+    # row blocks formed again between ordinary ones: the queries of the next block or head arrive meanwhile
+    assert _walk(lengths, L, Hq, Hkv) >= 2
+    g = np.random.default_rng(7)
+    n = sum(lengths)
+    at = np.concatenate([np.arange(N) for N in lengths])  # position in the prompt
+    far = {"first-low": at < 3, "first-high": at < 3, "middle": (at >= 200) & (at < 210), "scattered": at % 37 == 0,
+           "all": np.ones(n, bool)}[rows]
+    v = np.sign(g.standard_normal(dh)).astype(np.float32)
+    c = 90.0 / np.sqrt(dh) * (-1.0 if rows in ("first-low", "all") else 1.0)  # scores near -90 or 90 nats
+    K = I.f32_to_bf16_bits((v + 0.1 * g.standard_normal((L, n, Hkv, dh))).astype(np.float32))
+    q = g.standard_normal((L, n, Hq, dh))
+    q -= (q @ v)[..., None] * v / dh
+    q[:, far] = 0.5 * q[:, far] + c * v
+    Q = I.f32_to_bf16_bits(q.astype(np.float32))
+    cu = I.cu_seqlens_from_lengths(lengths)
+    rtol = _rtol(Q, K, dh ** -0.5, max(lengths))
+    Qd, Kd, cud = dev(Q), dev(K), dev(cu)
+    S = estp.attn_importance(Qd, Kd, cud, max(lengths))
+    ref = oracle.attn_importance(Q, K, cu)
+    print(f"{rows}: bound {rtol:.2e}, max rel |dS| / bound = {(np.abs(host(S) - ref) / ref / rtol).max():.3g}")
+    assert np.all(np.abs(host(S) - ref) <= rtol * ref)
+    assert torch.equal(S, estp.attn_importance(Qd, Kd, cud, max(lengths)))
+    X = host(estp.attn_importance_ex(Qd, Kd, cud, max(lengths), exclude_self=True))
+    ref = oracle.attn_importance(Q, K, cu, exclude_self=True)
+    assert np.all(np.abs(X - ref) <= rtol * ref + 2.0 ** -126)
