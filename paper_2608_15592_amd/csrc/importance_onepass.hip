@@ -137,7 +137,8 @@ __global__ __launch_bounds__(64 * W, 2) void attn_onepass_kernel(const uint16_t*
 #pragma unroll
     for (int q = 0; q < PI; ++q) lds_dma16_buf(r, k_off[q], 0, ring(w, to) + q * 1024);
   };
-  // ---- query tile of row block i, head share hh
+  // ---- query tile of row block i, head share hh.  Rows past the prompt take its last query again: zeros there
+  // would meet an infinite key feature as NaN, which a row weight of 0 does not keep out of the key's mass.
   auto issue_q = [&](int hh, int i, int buf) {
     const int rows = min(32, N - 32 * i);
     const buf_rsrc_t rq = make_rsrc(Qh + size_t(32 * i) * qrow + size_t(hh) * DH * 2,
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_onepass_kernel(const uint16_t*
 #pragma unroll
     for (int q = w; q < QI; q += W) {
       const int r = q * TQ::kRowsPerInst + lane / TQ::kChunks;
-      lds_dma16_buf(rq, uint32_t(r) * qrow + uint32_t(TQ::swz(r, lane % TQ::kChunks) * 16), 0, qbuf(buf) + q * 1024);
+      lds_dma16_buf(rq, uint32_t(min(r, rows - 1)) * qrow + uint32_t(TQ::swz(r, lane % TQ::kChunks) * 16), 0, qbuf(buf) + q * 1024);
     }
   };
 

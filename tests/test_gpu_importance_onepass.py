@@ -145,3 +145,25 @@ def test_onepass_sums_out_of_range_between_others(lengths, L, Hq, Hkv, dh, rows)
     X = host(estp.attn_importance_ex(Qd, Kd, cud, max(lengths), exclude_self=True))
     ref = oracle.attn_importance(Q, K, cu, exclude_self=True)
     assert np.all(np.abs(X - ref) <= rtol * ref + 2.0 ** -126)
+
+
+@pytest.mark.parametrize("rows", ["ordinary", "low"])
+@pytest.mark.parametrize("lengths", [[70], [1, 333, 64, 45]], ids=["70", "ragged"])
+def test_onepass_infinite_key_feature_gets_no_attention(lengths, rows):
+    # a key whose every score is -inf gets exactly 0, also where the last row block has rows past the prompt
+    dh = 64
+    Q, K, cu = _qk(lengths, 1, 4, 2, dh, 8)
+    q, k = I.bf16_bits_to_f32(Q), I.bf16_bits_to_f32(K)
+    q[..., 5] = 1.0
+    if rows == "low":  # every other score near -95 nats: the rows are formed again
+        q[..., 7], k[..., 7] = 32.0, -24.0
+    keys = [int(lo) + j for lo, N in zip(cu, lengths) for j in (1, N // 2, N - 1) if N > 1]
+    k[:, keys, :, 5] = -np.inf
+    Q, K = I.f32_to_bf16_bits(q), I.f32_to_bf16_bits(k)
+    S = host(estp.attn_importance(dev(Q), dev(K), dev(cu), max(lengths)))
+    ref = oracle.attn_importance(Q, K, cu)
+    assert np.all(S[keys] == 0)
+    rest = np.setdiff1d(np.arange(sum(lengths)), keys)
+    k[..., 5] = 0.0  # the bound of the finite scores
+    rtol = _rtol(Q, I.f32_to_bf16_bits(k), dh ** -0.5, max(lengths)) + 8 * U
+    assert np.all(np.abs(S[rest] - ref[rest]) <= rtol * ref[rest])
