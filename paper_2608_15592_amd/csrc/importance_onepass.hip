@@ -15,7 +15,13 @@
 // Exponentials are taken without a row maximum: fp32 holds 2^(c s) for
 // |c s| < 126 with the relative precision of the score itself.  A row block
 // with a live row whose sum leaves [2^-30, 2^100] (or is not a number) is
-// formed again with the rows' exact maxima.
+// formed again, and those after it are formed so at once while their rows need
+// it: each wave keeps the scores until it knows its own keys' row maxima, takes
+// those off, and the waves' sums and weights are put on one scale as they are
+// exchanged.  us per call on MI355X, ordinary scores, every row out of range, and
+// the two passes on the latter: 16 x 512 tokens, 32/8 heads of 128 66, 80 and 95,
+// 16 x 2048 581, 658 and 609; heads of 64 384, 490 and 427.  (Such a row block formed
+// three more times, a key block at a time, took 351, 4450 and 2780.)
 //
 // Keys stream through per-wave LDS rings of 32-key x 64-feature pieces
 // (buffer -> LDS transfers, no barrier: a wave reads only its own ring), across
@@ -44,23 +50,24 @@ namespace {
 
 constexpr int kBlocks = 8;  // most 32-key blocks per wave
 
-// Sum of v[r] over the 32 lanes of a half-wave, for each r of 16: lane l ends with the sum of
+// Sum (or maximum: op) of v[r] over the 32 lanes of a half-wave, for each r of 16: lane l ends with that of
 // r = l % 16 (butterflies that halve the values each step, then the two 16-lane rows).
 template <int kCtrl>
 __device__ __forceinline__ float dpp_mov(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xf, 0xf, true));
 }
-__device__ __forceinline__ float reduce16(const float (&v)[16], int lane) {
+template <typename Op>
+__device__ __forceinline__ float reduce16(const float (&v)[16], int lane, Op op) {
   float a[8], b[4], c[2];
   const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2, b0 = lane & 1;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) a[k] = (b3 ? v[k + 8] : v[k]) + dpp_mov<0x140>(b3 ? v[k] : v[k + 8]);  // row mirror
+  for (int k = 0; k < 8; ++k) a[k] = op(b3 ? v[k + 8] : v[k], dpp_mov<0x140>(b3 ? v[k] : v[k + 8]));  // row mirror
 #pragma unroll
-  for (int k = 0; k < 4; ++k) b[k] = (b2 ? a[k + 4] : a[k]) + dpp_mov<0x141>(b2 ? a[k] : a[k + 4]);  // half mirror
+  for (int k = 0; k < 4; ++k) b[k] = op(b2 ? a[k + 4] : a[k], dpp_mov<0x141>(b2 ? a[k] : a[k + 4]));  // half mirror
 #pragma unroll
-  for (int k = 0; k < 2; ++k) c[k] = (b1 ? b[k + 2] : b[k]) + dpp_mov<0x4e>(b1 ? b[k] : b[k + 2]);  // lane ^ 2
-  const float d = (b0 ? c[1] : c[0]) + dpp_mov<0xb1>(b0 ? c[0] : c[1]);                             // lane ^ 1
-  return d + __shfl_xor(d, 16, 64);
+  for (int k = 0; k < 2; ++k) c[k] = op(b1 ? b[k + 2] : b[k], dpp_mov<0x4e>(b1 ? b[k] : b[k + 2]));  // lane ^ 2
+  const float d = op(b0 ? c[1] : c[0], dpp_mov<0xb1>(b0 ? c[0] : c[1]));                             // lane ^ 1
+  return op(d, __shfl_xor(d, 16, 64));
 }
 
 // A value the compiler cannot see through: keeps the 16 diagonal masks of a lane (32 scalar
@@ -68,6 +75,15 @@ __device__ __forceinline__ float reduce16(const float (&v)[16], int lane) {
 __device__ __forceinline__ int opaque(int x) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm("" : "+v"(x));
+#endif
+  return x;
+}
+
+// The same for a uniform value: the pieces' addresses are formed in each row block from it, not once ahead of the
+// loops for all bodies, and spilled (128 scalar registers; 9 prompts of 45-1021 tokens 28.8 us, so 26.2).
+__device__ __forceinline__ uint32_t opaque_uniform(uint32_t x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("" : "+s"(x));
 #endif
   return x;
 }
@@ -90,11 +106,13 @@ __global__ __launch_bounds__(64 * W, 2) void attn_onepass_kernel(const uint16_t*
   constexpr int QI = kQTile / 1024;  // transfers per query tile, dealt over the waves
   // One shared array: several would be told apart by alias scopes, and the compiler then guards every
   // read of any of them with a wait for all transfers into LDS in flight.
-  constexpr int kRing = 0, kQ = W * S * kPiece, kZ = kQ + 2 * kQTile, kWt = kZ + 2 * W * 32 * 4;
+  constexpr int kRing = 0, kQ = W * S * kPiece, kZ = kQ + 2 * kQTile, kM = kZ + 2 * W * 32 * 4;
+  constexpr int kWt = kM + 2 * W * 32 * 4;
   __shared__ __attribute__((aligned(16))) char lds[kWt + W * 32 * 4];
   auto ring = [&](int wave, int slot) { return lds + kRing + (wave * S + slot) * kPiece; };
   auto qbuf = [&](int buf) { return lds + kQ + buf * kQTile; };
   auto zsum = [&](int buf, int wave) { return reinterpret_cast<float*>(lds + kZ) + (buf * W + wave) * 32; };
+  auto zmax = [&](int buf, int wave) { return reinterpret_cast<float*>(lds + kM) + (buf * W + wave) * 32; };
   auto wrow = [&](int wave) { return reinterpret_cast<float*>(lds + kWt) + wave * 32; };
 
   // workgroup -> (unit, share): an eighth of the units to each XCD, the shares of a unit (same keys)
@@ -131,8 +149,8 @@ __global__ __launch_bounds__(64 * W, 2) void attn_onepass_kernel(const uint16_t*
   }
   const uint32_t k_first = uint32_t(w) * 32u * krow, k_step = uint32_t(W) * 32u * krow;
   // piece idx (key block idx / NP of the wave, features PD (idx % NP) ...) into a slot
-  auto issue_piece = [&](int idx, int to) {
-    const uint32_t at = k_first + uint32_t(idx / NP) * k_step + uint32_t(idx % NP) * (PD * 2);
+  auto issue_piece = [&](int idx, int to, uint32_t first, uint32_t step) {
+    const uint32_t at = first + uint32_t(idx / NP) * step + uint32_t(idx % NP) * (PD * 2);
     const buf_rsrc_t r = make_rsrc(Kg + at, uint32_t(max(0, int(k_bytes) - int(at))));  // past the prompt: no access
 #pragma unroll
     for (int q = 0; q < PI; ++q) lds_dma16_buf(r, k_off[q], 0, ring(w, to) + q * 1024);
@@ -146,7 +164,8 @@ __global__ __launch_bounds__(64 * W, 2) void attn_onepass_kernel(const uint16_t*
 #pragma unroll
     for (int q = w; q < QI; q += W) {
       const int r = q * TQ::kRowsPerInst + lane / TQ::kChunks;
-      lds_dma16_buf(rq, uint32_t(min(r, rows - 1)) * qrow + uint32_t(TQ::swz(r, lane % TQ::kChunks) * 16), 0, qbuf(buf) + q * 1024);
+      lds_dma16_buf(rq, uint32_t(min(r, rows - 1)) * qrow + uint32_t(TQ::swz(r, lane % TQ::kChunks) * 16), 0,
+                    qbuf(buf) + q * 1024);
     }
   };
 
@@ -157,98 +176,38 @@ __global__ __launch_bounds__(64 * W, 2) void attn_onepass_kernel(const uint16_t*
   if (rs0 < nrb) {
     issue_q(0, rs0, 0);
 #pragma unroll
-    for (int q = 0; q < S - 1; ++q) issue_piece(q, q);
+    for (int q = 0; q < S - 1; ++q) issue_piece(q, q, k_first, k_step);
     wait_vm<0>();
     lds_barrier();
     int slot = 0, par = 0, i = rs0;  // slot: of the next piece to read; i: the row block
+    bool far = false;                // the last row block's sums were out of the plain form's range
     // acc[r] of a block: query 32 i + 8 (r / 4) + 4 half + r % 4, key 32 (w + W c) + col
 
-    // ---- the rare row block with a sum out of range, again with the rows' exact maxima: scores formed
-    // three times (maxima, sums, masses), one key block at a time.  Every wave takes it, since all read
-    // the same sums.  Adds its masses to csum.
-    auto exact_rows = [&](int cnt) {
-      const int lane = opaque(int(threadIdx.x) & 63), col = lane & 31, half = lane >> 5;
-      auto scores = [&](int c, f32x16_t& acc) {
-        const int kb = w + W * c;
-        const char* kr = Kg + size_t(min(32 * kb + col, N - 1)) * krow;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(qbuf(par) + TQ::off(col, ks * 2 + half));
-          const bf16x8_t k = *reinterpret_cast<const bf16x8_t*>(kr + (ks * 2 + half) * 16);
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, k, acc, 0, 0, 0);
-        }
-        if (kb == i) {
-          const int t = opaque(col - 4 * half);
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[r] = 8 * (r >> 2) + (r & 3) < t ? -INFINITY : acc[r];
-        }
-      };
-      auto out_row = [&](int r) { return 8 * (r >> 2) + 4 * half + (r & 3); };
-      float mx[16], rs[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        mx[r] = -INFINITY;
-        rs[r] = 0.f;
-      }
-      f32x16_t acc;
-      for (int c = 0; c < cnt; ++c) {
-        scores(c, acc);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx[r] = fmaxf(mx[r], acc[r]);
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        for (int o = 1; o <= 16; o <<= 1) mx[r] = fmaxf(mx[r], __shfl_xor(mx[r], o, 64));
-      __syncthreads();  // every wave has read the sums
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (col == 0) zsum(par, w)[out_row(r)] = mx[r];
-      __syncthreads();
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        for (int q = 0; q < W; ++q) mx[r] = fmaxf(mx[r], zsum(par, q)[out_row(r)]);
-      for (int c = 0; c < cnt; ++c) {
-        scores(c, acc);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) rs[r] += fast_exp2(fmaf(acc[r], c2, -mx[r] * c2));
-      }
-      const float z = reduce16(rs, lane);
-      __syncthreads();  // every wave has read the maxima
-      if ((lane & 16) == 0) zsum(par, w)[out_row(lane & 15)] = z;
-      __syncthreads();
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float Z = 0.f;
-        for (int q = 0; q < W; ++q) Z += zsum(par, q)[out_row(r)];
-        rs[r] = 32 * i + out_row(r) < N ? 1.f / Z : 0.f;
-      }
-      for (int c = 0; c < cnt; ++c) {
-        scores(c, acc);
-        const int t = w + W * c == i ? opaque(col - 4 * half + strict) : -32;
-        float s = 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          s += 8 * (r >> 2) + (r & 3) < t ? 0.f : fast_exp2(fmaf(acc[r], c2, -mx[r] * c2)) * rs[r];
-#pragma unroll
-        for (int k = 0; k < kBlocks; ++k) csum[k] += k == c ? s : 0.f;
-      }
-      // Every wave has read this row block's queries: the caller's next transfers go into their buffer, and a
-      // wave with few key blocks (none, in a prompt's first row blocks) would issue them while others still read.
-      __syncthreads();
-    };
-
     // ---- one row block against this wave's CNT key blocks; one body per CNT, so that the scores stay in
-    // the same registers from their products to their masses
-    auto row_block = [&](auto cnt_c) {
+    // the same registers from their products to their masses.  kMax: relative to the row maxima of the wave's
+    // keys.  Returns whether a live row's sum is out of the plain form's range: only with kMax are the masses
+    // added then.
+    auto row_block = [&](auto cnt_c, auto max_c) {
       constexpr int CNT = decltype(cnt_c)::value;
+      constexpr bool kMax = decltype(max_c)::value;
       const bool diag = CNT > 0 && w + W * (CNT - 1) == i;  // the last block holds the diagonal
       f32x16_t sc[CNT > 0 ? CNT : 1];
-      float rs[16];
+      float rs[16];  // row sums (kMax: at first the row maxima)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) rs[r] = 0.f;
+      for (int r = 0; r < 16; ++r) rs[r] = kMax && CNT > 0 ? -INFINITY : 0.f;
+      // 16 values of a row of 32, those of this lane's accumulator rows
+      auto rows_of = [&](const float* p, float (&v)[16]) {
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const float4 x = *reinterpret_cast<const float4*>(p + 8 * q4 + 4 * half);
+          v[4 * q4] = x.x;
+          v[4 * q4 + 1] = x.y;
+          v[4 * q4 + 2] = x.z;
+          v[4 * q4 + 3] = x.w;
+        }
+      };
       if constexpr (CNT > 0) {
+        const uint32_t kf = opaque_uniform(k_first), k_st = opaque_uniform(k_step);
         bf16x8_t aq[KS];
         const int qc = opaque(col);  // its addresses formed here, not kept through the loops
 #pragma unroll
@@ -257,15 +216,19 @@ __global__ __launch_bounds__(64 * W, 2) void attn_onepass_kernel(const uint16_t*
         auto exps = [&](f32x16_t& acc, int from, int to) {
 #pragma unroll
           for (int r = from; r < to; ++r) {
-            acc[r] = fast_exp2(acc[r] * c2);
-            rs[r] += acc[r];
+            if constexpr (kMax) {
+              rs[r] = fmaxf(rs[r], acc[r]);
+            } else {
+              acc[r] = fast_exp2(acc[r] * c2);
+              rs[r] += acc[r];
+            }
           }
         };
         // behind step q of the row block: the piece S - 1 further on, into the slot read last
         constexpr int kSteps = CNT * NP > S - 1 ? CNT * NP : S - 1;
         auto refill = [&](int q) {
           const int idx = q + S - 1 < kSteps ? q + S - 1 : q + S - 1 - kSteps;
-          issue_piece(idx, slot == 0 ? S - 1 : slot - 1);
+          issue_piece(idx, slot == 0 ? S - 1 : slot - 1, kf, k_st);
         };
 #pragma unroll
         for (int c = 0; c < CNT; ++c) {
@@ -309,37 +272,63 @@ __global__ __launch_bounds__(64 * W, 2) void attn_onepass_kernel(const uint16_t*
           for (int r = 0; r < 16; ++r) sc[CNT - 1][r] = 8 * (r >> 2) + (r & 3) < t ? -INFINITY : sc[CNT - 1][r];
         }
         exps(sc[CNT - 1], 0, 16);
+        if constexpr (kMax) {
+          // the wave's row maxima in base-2 units; rows whose every score is -inf stay above them, and add 0
+          const int ln = opaque(lane), out_row = 8 * ((ln & 15) >> 2) + 4 * half + (ln & 3);  // row of reduce16's value
+          const float m = fmaxf(reduce16(rs, ln, [](float x, float y) { return fmaxf(x, y); }) * c2, -1e30f);
+          if ((ln & 16) == 0) zmax(par, w)[out_row] = m;
+          __builtin_amdgcn_wave_barrier();
+          float ref[16];
+          rows_of(zmax(par, w), ref);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) rs[r] = 0.f;
+#pragma unroll
+          for (int c = 0; c < CNT; ++c)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              sc[c][r] = fast_exp2(fmaf(sc[c][r], c2, -ref[r]));
+              rs[r] += sc[c][r];
+            }
+        }
+      } else if constexpr (kMax) {
+        if (lane < 32) zmax(par, w)[lane] = -1e30f;
       }
 
       // row sums over the workgroup: one barrier (double buffered), which also publishes the next row
       // block's queries (older than the S - 1 pieces that follow this row block's)
       {
-        const int ln = opaque(lane);
-        const float z = reduce16(rs, ln);
-        if ((ln & 16) == 0) zsum(par, w)[8 * ((ln & 15) >> 2) + 4 * half + (ln & 3)] = z;
+        const int ln = opaque(lane), out_row = 8 * ((ln & 15) >> 2) + 4 * half + (ln & 3);
+        const float z = reduce16(rs, ln, [](float x, float y) { return x + y; });
+        if ((ln & 16) == 0) zsum(par, w)[out_row] = z;
       }
       if constexpr (CNT > 0)
         wait_vm<(S - 1) * PI>();
       else
         wait_vm<0>();
       lds_barrier();
-      float Z = 0.f;
-#pragma unroll
-      for (int q = 0; q < W; ++q) Z += zsum(par, q)[col];
       const bool live = 32 * i + col < N;
-      if (__builtin_expect(__any(live && !(Z >= 0x1p-30f && Z <= 0x1p100f)), 0)) return true;
-      if constexpr (CNT > 0) {
-        // this wave's copy of the row weights 1 / Z (0 past the prompt), 16 per lane
-        if (lane < 32) wrow(w)[col] = live ? 1.f / Z : 0.f;
-        float wt[16];
+      float Z = 0.f, M = 0.f;  // the row's sum is Z 2^M
+      bool out;
+      if constexpr (kMax) {
+        M = zmax(par, 0)[col];
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const float4 v = *reinterpret_cast<const float4*>(wrow(w) + 8 * q4 + 4 * half);
-          wt[4 * q4] = v.x;
-          wt[4 * q4 + 1] = v.y;
-          wt[4 * q4 + 2] = v.z;
-          wt[4 * q4 + 3] = v.w;
-        }
+        for (int q = 1; q < W; ++q) M = fmaxf(M, zmax(par, q)[col]);
+#pragma unroll
+        for (int q = 0; q < W; ++q) Z = fmaf(zsum(par, q)[col], fast_exp2(zmax(par, q)[col] - M), Z);
+        const float z2 = M + fast_log2(Z);
+        out = __any(live && !(z2 >= -30.f && z2 <= 100.f));
+      } else {
+#pragma unroll
+        for (int q = 0; q < W; ++q) Z += zsum(par, q)[col];
+        out = __any(live && !(Z >= 0x1p-30f && Z <= 0x1p100f));
+        if (__builtin_expect(out, 0)) return true;
+      }
+      if constexpr (CNT > 0) {
+        // this wave's copy of the row weights (0 past the prompt), 16 per lane
+        const float scale = kMax ? fast_exp2(zmax(par, w)[col] - M) : 1.f;
+        if (lane < 32) wrow(w)[col] = live ? scale / Z : 0.f;
+        float wt[16];
+        rows_of(wrow(w), wt);
 #pragma unroll
         for (int c = 0; c < CNT - 1; ++c) {
           float s0 = csum[c], s1 = 0.f;
@@ -358,7 +347,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_onepass_kernel(const uint16_t*
         for (int r = 0; r < 16; ++r) s0 += 8 * (r >> 2) + (r & 3) < t ? 0.f : sc[CNT - 1][r] * wt[r];
         csum[CNT - 1] += s0;
       }
-      return false;
+      return out;
     };
     for (int hh = 0; hh < hpw; ++hh)
       for (i = rs0; i < nrb; i += rsplit, par ^= 1) {
@@ -367,19 +356,27 @@ __global__ __launch_bounds__(64 * W, 2) void attn_onepass_kernel(const uint16_t*
         else if (hh + 1 < hpw)
           issue_q(hh + 1, rs0, par ^ 1);
         const int cnt = i >= w ? (i - w) / W + 1 : 0;  // key blocks of this wave up to the diagonal
-        bool bad;
-        switch (cnt) {
-          case 0: bad = row_block(std::integral_constant<int, 0>{}); break;
-          case 1: bad = row_block(std::integral_constant<int, 1>{}); break;
-          case 2: bad = row_block(std::integral_constant<int, 2>{}); break;
-          case 3: bad = row_block(std::integral_constant<int, 3>{}); break;
-          case 4: bad = row_block(std::integral_constant<int, 4>{}); break;
-          case 5: bad = row_block(std::integral_constant<int, 5>{}); break;
-          case 6: bad = row_block(std::integral_constant<int, 6>{}); break;
-          case 7: bad = row_block(std::integral_constant<int, 7>{}); break;
-          default: bad = row_block(std::integral_constant<int, 8>{}); break;
+        auto go = [&](auto max_c) {
+          switch (cnt) {
+            case 0: return row_block(std::integral_constant<int, 0>{}, max_c);
+            case 1: return row_block(std::integral_constant<int, 1>{}, max_c);
+            case 2: return row_block(std::integral_constant<int, 2>{}, max_c);
+            case 3: return row_block(std::integral_constant<int, 3>{}, max_c);
+            case 4: return row_block(std::integral_constant<int, 4>{}, max_c);
+            case 5: return row_block(std::integral_constant<int, 5>{}, max_c);
+            case 6: return row_block(std::integral_constant<int, 6>{}, max_c);
+            case 7: return row_block(std::integral_constant<int, 7>{}, max_c);
+            default: return row_block(std::integral_constant<int, 8>{}, max_c);
+          }
+        };
+        // the same in every wave, which all read the same sums
+        if (!far) {
+          far = go(std::false_type{});
+          // again: the pieces in flight are this wave's first ones and the queries are still there; every wave
+          // has read the sums before they are written again
+          if (__builtin_expect(far, 0)) __syncthreads();
         }
-        if (__builtin_expect(bad, 0)) exact_rows(cnt);
+        if (__builtin_expect(far, 0)) far = go(std::true_type{});
       }
     wait_vm<0>();  // no transfer into LDS outlives the workgroup
   }
