@@ -59,7 +59,7 @@ typedef enum estp_status {
   ESTP_OK = 0,
   ESTP_ERR_INVALID_ARG = 1, /* null pointer, bad size, bad alignment, bad hyperparameter */
   ESTP_ERR_UNSUPPORTED = 2, /* valid but not implemented (dtype, head_dim) */
-  ESTP_ERR_WORKSPACE = 3,   /* workspace smaller than *_workspace_size() */
+  ESTP_ERR_WORKSPACE = 3,   /* workspace smaller than the call needs */
   ESTP_ERR_HIP = 4          /* a HIP runtime call or kernel launch failed */
 } estp_status;
 
@@ -176,6 +176,13 @@ ESTP_API int estp_token_entropy_noalloc(const void* X, const void* W, int64_t n_
  *   dtype                   ESTP_BF16 (matrix-core scores, fp32 accumulation) or
  *                           ESTP_F32 (fp32 FMAs throughout); Q and K alike
  * Requires Hq % Hkv == 0, dh in {32, 64, 128}, 1 <= max_seqlen.
+ *
+ * Workspace: the size returned does not grow with the prompt throughout, since
+ * the one pass of a short prompt can take more than the two passes of a longer
+ * one.  A smaller workspace is taken down to what the two passes of this call
+ * need, and then runs those: one sized for prompts twice as long (same batch,
+ * layers and heads) always serves.  S then differs in its last bits, as between
+ * any two forms of the call.
  * ------------------------------------------------------------------------ */
 ESTP_API size_t estp_attn_importance_workspace_size(int64_t n_tok, int32_t B, int32_t max_seqlen, int32_t L, int32_t Hq,
                                            int32_t Hkv, int32_t dh, int dtype);

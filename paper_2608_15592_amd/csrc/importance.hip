@@ -69,10 +69,6 @@ inline size_t block_rows(int64_t n_tok, int32_t B, int32_t max_seqlen) {
   return use_block_list(n_tok, B, max_seqlen) ? block_bound(n_tok, B, max_seqlen) : size_t(B) * nqb;
 }
 
-// Column-mass rows of a call: one per (layer, KV head) times the shares of whichever kernel it takes.
-size_t part_rows(int64_t n_tok, int32_t B, int32_t max_seqlen, int32_t L, int32_t Hq, int32_t Hkv, int32_t dh,
-                 bool f32, bool with_lse);
-
 // Query heads of one KV group are split over `nsplit` pass-2 workgroups when the grid would
 // otherwise be small: the smallest divisor of G = Hq / Hkv that gives at least four workgroups per
 // compute unit (else G, one head each).  The fp32 kernels keep one workgroup per group.
@@ -516,19 +512,50 @@ std::vector<int2> block_list_on_host(const std::vector<int>& cu, int B, int nblk
   return out;
 }
 
-size_t part_rows(int64_t n_tok, int32_t B, int32_t max_seqlen, int32_t L, int32_t Hq, int32_t Hkv, int32_t dh,
-                 bool f32, bool with_lse) {
+// The two passes' arrays in a workspace, and the bytes they take.
+struct TwoPassArrays {
+  float* lse2;   // row log-sum-exps [L, Hq, n_tok], unless the caller gives them
+  float* part;   // column masses [L, Hkv * nsplit, n_tok]
+  int2* blist;   // live 256-row blocks
+  size_t bytes;
+};
+TwoPassArrays carve_two_passes(void* workspace, int64_t n_tok, int32_t B, int32_t max_seqlen, int32_t L, int32_t Hq,
+                               int32_t Hkv, bool f32, bool with_lse) {
+  Carver c(workspace);
+  TwoPassArrays a;
+  a.lse2 = with_lse ? nullptr : c.take<float>(size_t(L) * Hq * n_tok);
+  a.part = c.take<float>(size_t(L) * Hkv * colsum_split(n_tok, B, max_seqlen, L, Hq, Hkv, f32) * n_tok);
+  a.blist = c.take<int2>(block_bound(n_tok, B, max_seqlen));
+  a.bytes = c.bytes();
+  return a;
+}
+
+// The one pass takes column masses alone, but for a short prompt more of them than a longer one's two passes take in
+// all (32/8 heads: 1 x 2048 tokens 8.4 MB, 1 x 32768 5.2 MB).  The size that callers are told holds both forms; a
+// workspace that holds only the two passes', such as one sized for a longer prompt, runs those.
+size_t onepass_bytes(const OnepassPlan& one, int64_t n_tok, int32_t L, int32_t Hkv) {
+  Carver c(nullptr);
+  if (one.waves) c.take<float>(size_t(L) * Hkv * one.hsplit * one.rsplit * n_tok);
+  return c.bytes();
+}
+size_t importance_bytes(int64_t n_tok, int32_t B, int32_t max_seqlen, int32_t L, int32_t Hq, int32_t Hkv, int32_t dh,
+                        bool f32, bool with_lse) {
   const OnepassPlan one = plan_onepass(n_tok, B, max_seqlen, L, Hq, Hkv, dh, f32, with_lse);
-  const int shares = one.waves ? one.hsplit * one.rsplit : colsum_split(n_tok, B, max_seqlen, L, Hq, Hkv, f32);
-  return size_t(L) * Hkv * shares;
+  return std::max(carve_two_passes(nullptr, n_tok, B, max_seqlen, L, Hq, Hkv, f32, with_lse).bytes,
+                  onepass_bytes(one, n_tok, L, Hkv));
 }
 
 template <int DH>
 int launch(const char* fn, const void* Qv, const void* Kv, bool f32, const int* cu, int B, int max_seqlen, int n_tok,
            int L, int Hq, int Hkv, float scale, const float* lse_in, int strict, const float* layer_weights, float* S,
-           float* lse2, float* part, int2* blist, hipStream_t s) {
-  const int nsplit = colsum_split(n_tok, B, max_seqlen, L, Hq, Hkv, f32);  // part holds L * Hkv * nsplit rows
-  const OnepassPlan one = plan_onepass(n_tok, B, max_seqlen, L, Hq, Hkv, DH, f32, lse_in != nullptr);
+           void* workspace, size_t workspace_bytes, hipStream_t s) {
+  const int nsplit = colsum_split(n_tok, B, max_seqlen, L, Hq, Hkv, f32);
+  const TwoPassArrays ws = carve_two_passes(workspace, n_tok, B, max_seqlen, L, Hq, Hkv, f32, lse_in != nullptr);
+  OnepassPlan one = plan_onepass(n_tok, B, max_seqlen, L, Hq, Hkv, DH, f32, lse_in != nullptr);
+  if (onepass_bytes(one, n_tok, L, Hkv) > workspace_bytes) one.waves = 0;
+  float* lse2 = ws.lse2;
+  float* part = one.waves ? static_cast<float*>(workspace) : ws.part;
+  int2* blist = ws.blist;
   static_assert(kQBlock == kKBlock, "the two passes share one list of 256-row blocks");
   const float c2 = scale * kLog2e;
   const int nqb = (max_seqlen + kQBlock - 1) / kQBlock;
@@ -618,17 +645,17 @@ int check_importance_args(const char* fn, const void* Q, const void* K, const in
 
 int launch_dh(const char* fn, int dh, const void* q, const void* k, bool f32, const int* cu, int B, int max_seqlen,
               int n, int L, int Hq, int Hkv, float scale, const float* lse_in, int strict, const float* lw, float* S,
-              float* lse2, float* part, int2* blist, hipStream_t s) {
+              void* workspace, size_t workspace_bytes, hipStream_t s) {
   switch (dh) {
     case 32:
-      return launch<32>(fn, q, k, f32, cu, B, max_seqlen, n, L, Hq, Hkv, scale, lse_in, strict, lw, S, lse2, part,
-                        blist, s);
+      return launch<32>(fn, q, k, f32, cu, B, max_seqlen, n, L, Hq, Hkv, scale, lse_in, strict, lw, S, workspace,
+                        workspace_bytes, s);
     case 64:
-      return launch<64>(fn, q, k, f32, cu, B, max_seqlen, n, L, Hq, Hkv, scale, lse_in, strict, lw, S, lse2, part,
-                        blist, s);
+      return launch<64>(fn, q, k, f32, cu, B, max_seqlen, n, L, Hq, Hkv, scale, lse_in, strict, lw, S, workspace,
+                        workspace_bytes, s);
     default:
-      return launch<128>(fn, q, k, f32, cu, B, max_seqlen, n, L, Hq, Hkv, scale, lse_in, strict, lw, S, lse2, part,
-                         blist, s);
+      return launch<128>(fn, q, k, f32, cu, B, max_seqlen, n, L, Hq, Hkv, scale, lse_in, strict, lw, S, workspace,
+                        workspace_bytes, s);
   }
 }
 
@@ -637,11 +664,7 @@ int launch_dh(const char* fn, int dh, const void* q, const void* k, bool f32, co
 extern "C" size_t estp_attn_importance_workspace_size(int64_t n_tok, int32_t B, int32_t max_seqlen, int32_t L,
                                                       int32_t Hq, int32_t Hkv, int32_t dh, int dtype) {
   if (n_tok < 1 || B < 1 || max_seqlen < 1 || L < 1 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0) return 0;
-  Carver c(nullptr);
-  c.take<float>(size_t(L) * Hq * n_tok);   // lse2 [L, Hq, n_tok]
-  c.take<float>(part_rows(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype == ESTP_F32, false) * n_tok);
-  c.take<int2>(block_bound(n_tok, B, max_seqlen));  // list of live 256-row blocks
-  return c.bytes();
+  return importance_bytes(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype == ESTP_F32, false);
 }
 
 extern "C" int estp_attn_importance(const void* Q, const void* K, const int32_t* cu_seqlens, int32_t B,
@@ -652,29 +675,23 @@ extern "C" int estp_attn_importance(const void* Q, const void* K, const int32_t*
   const int st = check_importance_args("estp_attn_importance", Q, K, cu_seqlens, B, max_seqlen, n_tok, L, Hq, Hkv,
                                        dh, scale, dtype, S);
   if (st != ESTP_OK) return st;
-  const size_t need = estp_attn_importance_workspace_size(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype);
+  const size_t need =
+      carve_two_passes(nullptr, n_tok, B, max_seqlen, L, Hq, Hkv, dtype == ESTP_F32, false).bytes;
   ESTP_REQUIRE(workspace_bytes >= need, ESTP_ERR_WORKSPACE,
                "estp_attn_importance: workspace of %zu bytes, %zu needed", workspace_bytes, need);
   ESTP_REQUIRE(workspace && aligned(workspace, 256), ESTP_ERR_INVALID_ARG,
                "estp_attn_importance: workspace must be non-null and 256-byte aligned");
 
-  Carver c(workspace);
-  float* lse2 = c.take<float>(size_t(L) * Hq * n_tok);
-  float* part =
-      c.take<float>(part_rows(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype == ESTP_F32, false) * n_tok);
-  int2* blist = c.take<int2>(block_bound(n_tok, B, max_seqlen));
   return launch_dh("estp_attn_importance", dh, Q, K, dtype == ESTP_F32, cu_seqlens, B, max_seqlen, int(n_tok), L, Hq,
-                   Hkv, scale, nullptr, 0, nullptr, S, lse2, part, blist, static_cast<hipStream_t>(stream));
+                   Hkv, scale, nullptr, 0, nullptr, S, workspace, workspace_bytes,
+                   static_cast<hipStream_t>(stream));
 }
 
 extern "C" size_t estp_attn_importance_from_lse_workspace_size(int64_t n_tok, int32_t B, int32_t max_seqlen,
                                                                int32_t L, int32_t Hq, int32_t Hkv, int32_t dh,
                                                                int dtype) {
   if (n_tok < 1 || B < 1 || max_seqlen < 1 || L < 1 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0) return 0;
-  Carver c(nullptr);
-  c.take<float>(part_rows(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype == ESTP_F32, true) * n_tok);
-  c.take<int2>(block_bound(n_tok, B, max_seqlen));  // list of live 256-row blocks
-  return c.bytes();
+  return importance_bytes(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype == ESTP_F32, true);
 }
 
 extern "C" int estp_attn_importance_from_lse(const void* Q, const void* K, const float* lse,
@@ -686,18 +703,15 @@ extern "C" int estp_attn_importance_from_lse(const void* Q, const void* K, const
                                        Hq, Hkv, dh, scale, dtype, S);
   if (st != ESTP_OK) return st;
   ESTP_REQUIRE(lse != nullptr, ESTP_ERR_INVALID_ARG, "estp_attn_importance_from_lse: lse must be non-null");
-  const size_t need = estp_attn_importance_from_lse_workspace_size(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype);
+  const size_t need =
+      carve_two_passes(nullptr, n_tok, B, max_seqlen, L, Hq, Hkv, dtype == ESTP_F32, true).bytes;
   ESTP_REQUIRE(workspace_bytes >= need, ESTP_ERR_WORKSPACE,
                "estp_attn_importance_from_lse: workspace of %zu bytes, %zu needed", workspace_bytes, need);
   ESTP_REQUIRE(workspace && aligned(workspace, 256), ESTP_ERR_INVALID_ARG,
                "estp_attn_importance_from_lse: workspace must be non-null and 256-byte aligned");
 
-  Carver c(workspace);
-  float* part =
-      c.take<float>(part_rows(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype == ESTP_F32, true) * n_tok);
-  int2* blist = c.take<int2>(block_bound(n_tok, B, max_seqlen));
   return launch_dh("estp_attn_importance_from_lse", dh, Q, K, dtype == ESTP_F32, cu_seqlens, B, max_seqlen,
-                   int(n_tok), L, Hq, Hkv, scale, lse, 0, nullptr, S, nullptr, part, blist,
+                   int(n_tok), L, Hq, Hkv, scale, lse, 0, nullptr, S, workspace, workspace_bytes,
                    static_cast<hipStream_t>(stream));
 }
 
@@ -725,17 +739,12 @@ extern "C" int estp_attn_importance_ex(const void* Q, const void* K, const float
       ESTP_REQUIRE(layer_weights[l] == layer_weights[l] && fabsf(layer_weights[l]) < INFINITY, ESTP_ERR_INVALID_ARG,
                    "estp_attn_importance_ex: layer weight %d is not finite", l);
   const size_t need =
-      estp_attn_importance_ex_workspace_size(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype, lse != nullptr);
+      carve_two_passes(nullptr, n_tok, B, max_seqlen, L, Hq, Hkv, dtype == ESTP_F32, lse != nullptr).bytes;
   ESTP_REQUIRE(workspace_bytes >= need, ESTP_ERR_WORKSPACE,
                "estp_attn_importance_ex: workspace of %zu bytes, %zu needed", workspace_bytes, need);
   ESTP_REQUIRE(workspace && aligned(workspace, 256), ESTP_ERR_INVALID_ARG,
                "estp_attn_importance_ex: workspace must be non-null and 256-byte aligned");
-  Carver c(workspace);
-  float* lse2 = lse ? nullptr : c.take<float>(size_t(L) * Hq * n_tok);
-  float* part =
-      c.take<float>(part_rows(n_tok, B, max_seqlen, L, Hq, Hkv, dh, dtype == ESTP_F32, lse != nullptr) * n_tok);
-  int2* blist = c.take<int2>(block_bound(n_tok, B, max_seqlen));
   return launch_dh("estp_attn_importance_ex", dh, Q, K, dtype == ESTP_F32, cu_seqlens, B, max_seqlen, int(n_tok), L,
-                   Hq, Hkv, scale, lse, (flags & ESTP_IMPORTANCE_EXCLUDE_SELF) ? 1 : 0, layer_weights, S, lse2, part,
-                   blist, static_cast<hipStream_t>(stream));
+                   Hq, Hkv, scale, lse, (flags & ESTP_IMPORTANCE_EXCLUDE_SELF) ? 1 : 0, layer_weights, S, workspace,
+                   workspace_bytes, static_cast<hipStream_t>(stream));
 }
