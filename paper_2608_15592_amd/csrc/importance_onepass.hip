@@ -408,16 +408,41 @@ size_t onepass_grid(const OnepassPlan& p, int B, int L, int Hkv) {
 
 }  // namespace
 
+// Whether row shares of heads of 32 or 64, up to 1024 tokens and with few KV heads, end in so many workgroups of a row
+// block or two that the two passes are faster: an estimate of both in us, fitted to 1200 calls of random shapes on
+// MI355X (row blocks, key blocks of the busiest wave and workgroups over the 512 resident, and the column masses; each
+// estimate within 20% of nearly every call).  Two passes and one, 166 prompts of up to 335 tokens, 7/1 heads of 64 65
+// and 88, 170 of 230, 6/2 of 32 34.6 and 41, 61 of 171-342, 28/4 of 64 82 and 118.  With eight KV heads, and below
+// 4096 tokens, the one pass was the faster one or within a few us.
+bool shares_too_fine(const OnepassPlan& p, int64_t n_tok, int B, int L, int Hq, int Hkv, int dh) {
+  if (dh == 128 || p.waves != 4 || Hkv > 4 || n_tok < 4096) return false;
+  const float n = float(n_tok), heads = float(L) * float(Hq), scores = heads * n * (n / float(B));  // as if equal
+  const float row_blocks = heads * (n / 32.f + float(B) / 2.f), key_blocks = scores / 8192.f + 0.4f * row_blocks;
+  const float shares = float(L) * float(Hkv) * float(p.rsplit * p.hsplit);
+  const float one = 8.5f + (1.25f * row_blocks + (dh == 32 ? 0.25f : 0.38f) * key_blocks + shares * float(B)) / 512.f +
+                    6e-6f * shares * n;
+  const float two = 27.f + 1.4f * scores / (8192.f * 768.f) + (dh == 32 ? 6e-6f : 25e-6f) * heads * n;
+  return one > 0.95f * two;
+}
+
 // One pass for prompts of up to 2048 tokens where it is the faster one.  us per call on MI355X, two passes and
 // one, 32/8 heads of 128, 1 layer: 1 x 500 tokens 45 and 20, 1 x 2048 128 and 70, 16 x 512 83 and 66, 600 x 64
-// 217 and 166, 32 x 1024 380 and 335, 32 x 2048 1290 and 1150 (4 layers: 5450 and 4600).  Two passes stay
+// 217 and 166, 32 x 1024 380 and 335, 32 x 2048 1290 and 1150 (4 layers: 5489 and 4340).  Two passes stay
 // - for batches of mixed lengths unless they are small: every workgroup walks whole rows of its prompt, so the
 //   longest prompts decide (64 prompts of 32-2048 tokens 485 and 630, 16 of them 148 and 267; 9 prompts of
-//   45-1021 tokens, 12/2 heads 67 and 39; 30 of 500-900 210 and 171);
+//   45-1021 tokens, 12/2 heads 67 and 28; 30 of 500-900 210 and 171);
 // - for large calls with smaller heads, whose scores cost less to form again (heads of 64: 16 x 2048 438 and
-//   402, 32 x 512 with 4 layers 310 and 316, 100 x 100 55 and 59; heads of 32: 20 x 1500 249 and 264).
+//   402, 32 x 512 with 4 layers 310 and 316, 100 x 100 55 and 59; heads of 32: 20 x 1500 249 and 264);
+// - past 1024 tokens, where workgroups of eight waves leave most of their last key blocks idle, for all but small
+//   calls: with heads of 32 and 64 (1051 tokens, 16/4 heads of 64 166 and 206; 69 prompts of 593-1187 262 and 306;
+//   1156 tokens, 8/1 of 32 72 and 96; equal prompts near 2048 gain with heads of 64, 27 x 1920, 24/8 486 and 448), and
+//   with heads of 128 where lengths differ (8 prompts of 524-1048, 48/8 heads 136 and 158; equal, 24/8 at 1544 tokens
+//   839 and 772);
+// - where the shares get too fine.
 // Shares: row blocks over up to 8 workgroups (they stream the same keys through one L2) of at least 16 row
-// blocks each while there are enough workgroups, then more, then a group's heads, then single row blocks.
+// blocks each while there are enough workgroups, then more, then a group's heads, then single row blocks.  A group
+// of a prime number of heads stays whole where its split would give more than twice the workgroups wanted and half of
+// them are there (61 prompts of 171-342 tokens, 28/4 heads of 64: 118 split, 80 whole).
 OnepassPlan plan_onepass(int64_t n_tok, int B, int max_seqlen, int L, int Hq, int Hkv, int dh, bool f32,
                          bool with_lse) {
   OnepassPlan p{0, 1, 1};
@@ -431,14 +456,25 @@ OnepassPlan plan_onepass(int64_t n_tok, int B, int max_seqlen, int L, int Hq, in
   if (dh < 128 && wgs >= size_t(dh == 64 && max_seqlen > 256 ? 24 : 8) * n_cu) return p;
   const int G = Hq / Hkv, nrb = (max_seqlen + 31) / 32;
   const int waves = max_seqlen <= 1024 ? 4 : 8;
+  const bool few = wgs * 2 < 7 * n_cu;
+  if (waves == 8 && !few) {
+    const bool differ = size_t(n_tok) * 20 < size_t(B) * max_seqlen * 19;  // the mean under 95% of the longest
+    if (dh == 128 ? differ && max_seqlen <= 1408 : dh < 64 || differ || max_seqlen <= 1792) return p;
+  }
   const size_t want = size_t(waves == 8 ? 4 : 8) * n_cu;
   const size_t units = size_t(B) * L * Hkv;
   p.rsplit = std::max(1, std::min(8, G * nrb / 16));
   while (p.rsplit < std::min(8, nrb) && units * p.rsplit < want) ++p.rsplit;
-  while (p.hsplit < G && (G % p.hsplit != 0 || units * p.rsplit * p.hsplit < want)) ++p.hsplit;
+  for (int h = 2; h <= G && units * p.rsplit * p.hsplit < want; ++h)
+    if (G % h == 0) {
+      if (units * p.rsplit * h > 2 * want && units * p.rsplit * p.hsplit * 2 >= want) break;
+      p.hsplit = h;
+    }
   if (units * p.rsplit * p.hsplit < want)
     p.rsplit = int(std::min<size_t>(nrb, (want + units * p.hsplit - 1) / (units * p.hsplit)));
-  p.waves = fits_launch(onepass_grid(p, B, L, Hkv), size_t(64) * waves) ? waves : 0;
+  if (!fits_launch(onepass_grid(p, B, L, Hkv), size_t(64) * waves)) return p;
+  p.waves = waves;
+  if (shares_too_fine(p, n_tok, B, L, Hq, Hkv, dh)) p.waves = 0;
   return p;
 }
 

@@ -114,7 +114,7 @@ def _walk(lengths, L, Hq, Hkv):
 
 
 # workgroups of four and of eight waves that walk several row blocks of several heads
-WALK_CASES = [([512] * 16, 1, 32, 8, 128), ([1057] * 8, 1, 32, 8, 32), ([330, 500, 441] * 11, 1, 8, 4, 64)]
+WALK_CASES = [([512] * 16, 1, 32, 8, 128), ([1057] * 4, 1, 32, 8, 32), ([330, 500, 441] * 11, 1, 8, 4, 64)]
 
 
 @pytest.mark.parametrize("rows", ["first-low", "first-high", "middle", "scattered", "all", "spread"])
