@@ -221,7 +221,8 @@ def test_importance_ex_variants_parity(lengths, L, Hq, Hkv, dh, qs, tag):
 @pytest.mark.parametrize("f32", [False, True], ids=["bf16", "f32"])
 def test_importance_accepts_a_larger_max_seqlen(f32):
     # max_seqlen is an upper bound on the prompt lengths (at most n_tok): a looser one changes the
-    # grids (blocks past every prompt, the list of live blocks, the head split) but not the result
+    # grids (fp32: blocks past every prompt, the list of live blocks; bf16 takes one
+    # pass here, and another share of its row blocks per workgroup) but not the result
     Q, K, cu = _qk([70, 1100, 9, 300], 2, 4, 2, 64, 1.0, 21)
     if f32:
         Q, K = oracle.widen(Q).astype(np.float32), oracle.widen(K).astype(np.float32)
