@@ -704,7 +704,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void entropy_gemm_kernel(
 // that folds them tile by tile, one token per lane, with the same fold (128 tokens a workgroup: one tile at a
 // time, two waves).  entropy_few_merge_kernel merges the states in the order the lanes, halves and slices do
 // there.  Bound by the supply of W and X into LDS (48 KB a stage, 25 B per cycle and CU as in the large
-// kernel, against 1024 cycles of matrix-core work) and, for one block of tokens, by HBM (4.2 TB/s).  us per
+// kernel, against 1024 cycles of matrix-core work) and, for one block of tokens, by HBM (3.9 TB/s).  us per
 // call on MI355X, 16 slices and this, V 128256, d 4096: 61 tokens 2190 and 266, 256 2285 and 316, 719 2260 and
 // 811, 1500 2270 and 1590; d 2048: 61 tokens 1177 and 145, 1024 1218 and 608.
 constexpr int kFewTiles = 8;    // vocabulary tiles per product
@@ -973,8 +973,9 @@ inline bool use_few(int64_t n_tok, int d, int n_vt) {
 // among equal maxima).  The tokens are first .. first + n, their states [n_slices, n].  kLanes
 // threads share a token: thread group q merges slices q, q + kLanes, ... in order, then the groups
 // merge in order (within a wave by lane exchange, then the four waves through LDS).  One thread per
-// token for 16 slices; 16 where a small call has up to 256 (61 and 719 tokens, 251 and 84 slices, on
-// MI355X: 21 us with one thread per token, 5.6 with 16).
+// token for 16 slices; 16 where a call's last tiles have more (MI355X, us with one thread per token and with
+// 16: the last token of 4097, 251 slices, 18.7 and 5.4; the last 904 of 5000, 63 slices, 9.1 and 5.1; 2500
+// tokens, 25 slices, 6.1 and 5.4).
 template <int kLanes>
 __global__ __launch_bounds__(256) void entropy_merge_kernel(const float* __restrict__ part_m,
                                                             const float* __restrict__ part_s,

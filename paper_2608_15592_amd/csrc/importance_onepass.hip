@@ -427,10 +427,10 @@ bool shares_too_fine(const OnepassPlan& p, int64_t n_tok, int B, int L, int Hq, 
 
 // One pass for prompts of up to 2048 tokens where it is the faster one.  us per call on MI355X, two passes and
 // one, 32/8 heads of 128, 1 layer: 1 x 500 tokens 45 and 20, 1 x 2048 128 and 70, 16 x 512 83 and 66, 600 x 64
-// 217 and 166, 32 x 1024 380 and 335, 32 x 2048 1290 and 1150 (4 layers: 5489 and 4340).  Two passes stay
+// 217 and 166, 32 x 1024 380 and 335, 32 x 2048 1290 and 1150 (4 layers: 5422 and 4293).  Two passes stay
 // - for batches of mixed lengths unless they are small: every workgroup walks whole rows of its prompt, so the
 //   longest prompts decide (64 prompts of 32-2048 tokens 485 and 630, 16 of them 148 and 267; 9 prompts of
-//   45-1021 tokens, 12/2 heads 67 and 28; 30 of 500-900 210 and 171);
+//   45-1021 tokens, 12/2 heads 67 and 27; 30 of 500-900 210 and 171);
 // - for large calls with smaller heads, whose scores cost less to form again (heads of 64: 16 x 2048 438 and
 //   402, 32 x 512 with 4 layers 310 and 316, 100 x 100 55 and 59; heads of 32: 20 x 1500 249 and 264);
 // - past 1024 tokens, where workgroups of eight waves leave most of their last key blocks idle, for all but small
